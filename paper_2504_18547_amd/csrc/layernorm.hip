@@ -3,14 +3,20 @@
 //
 // Phase 1 -- row statistics.  They are the incremental recurrences of Eq. 5 in fp32, elements in
 // order: that order is part of the definition (fp32 addition does not associate), so one LANE
-// walks one row and the parallelism is across the 64 rows of a workgroup (one of its four waves).  The lane streams
-// its row in chunks of 16 elements, the next chunk requested before the current one is used.
+// walks one row.  What bounds it is the serial chain: a wave issues one VALU instruction per 8.5
+// cycles, dependent or not, so the time is (instructions per element of the busiest wave) x 8.5
+// cycles x columns whatever the number of rows.  The work of a step is therefore dealt to three
+// waves of the workgroup that run one chunk of CH columns apart:
+//   walker      mu_i = mu_{i-1} + (x_i - mu_{i-1}) / i        (four instructions; leaves mu_i in LDS)
+//   accumulator M_i  = M_{i-1} + (x_i - mu_{i-1}) * (x_i - mu_i)      (four)
+//   checker     smallest nonzero |x_i - mu_{i-1}|: is the division-free step exact?   (four)
+// while four more waves bring the rows in, coalesced, several chunks ahead.
 // Phase 2 -- levels.  The quantizer is the comparator of Fig. 5(b): the level is the number of
 // references (k - 1/2)*step that the normalised value exceeds, each decided as
 //     ssq((x - mu) * gamma) * n  >  ssq((k - 1/2)*step - beta) * V,      ssq(v) = v * |v|,
 // V = M_n + n*eps the (stabilised) sum of squared deviations -- sigma never appears.  Elements
-// are independent here, so the workgroup's rows are re-read wave by wave with coalesced 16-byte
-// loads by all four waves, four elements per lane, one row at a time, the next row in flight.  The comparisons are monotone in k, so
+// are independent here, so the workgroup's rows are re-read (from L2) wave by wave with coalesced
+// 16-byte loads by all waves, four elements per lane, one row at a time, the next row in flight.  The comparisons are monotone in k, so
 // instead of all 2^b - 1 of them the kernel makes a guess with the hardware reciprocal square
 // root.  A guess that lies further from every half-integer than the proven distance between the
 // guess and the comparator's own boundary stands as it is; otherwise the comparator itself is
@@ -24,264 +30,466 @@ namespace vitq {
 
 namespace {
 
-// RN(1/k), k = 1 .. kRkMax, evaluated by the compiler (IEEE division).  With rk = RN(1/k):
-//     q0 = RN(d*rk),  r = d - q0*k (exact in one FMA),  q = RN(q0 + r*rk)
-// equals RN(d/k) for EVERY fp32 significand of d and every k <= 16384 -- checked exhaustively on
-// the CPU (2^23 significands x 16384 divisors, no mismatch) -- and the exponent of d only scales
-// all three steps, as long as q0 stays a normal number and nothing overflows: 2^-100 <= |d| <= 2^120.
-#ifndef VITQ_LN_RB
-#define VITQ_LN_RB 1      // rows a wave decides per batch in phase 2 (more cost registers, hence resident waves)
-#endif
-#ifndef VITQ_LN_CH
-#define VITQ_LN_CH 16      // elements a lane requests at a time in phase 1
-#endif
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// 1/k, k = 1 .. kRkMax, as hi + lo: hi = RN(1/k), lo = RN(1/k - hi), evaluated by the compiler.  Then
+//     t = RN(d*lo),  q = RN(d*hi + t)          (a multiply and an FMA)
+// equals RN(d/k) for every fp32 d with 2^-98 <= |d| and a finite result, and for d = 0: hi + lo and the
+// rounding of t are off by at most 2^-48 of the quotient together, while d/k is never the midpoint of two
+// neighbouring fp32 numbers (a midpoint has a 25-bit odd significand, which would have to divide the 24-bit
+// one of d) and never closer to one than 1/(2k) of their distance, i.e. 2^-37 of the quotient for
+// k <= 4096.  (tests/test_division_free_mean_update.py runs a slice of that space.)  An infinite or NaN d
+// gives a mean that is not finite from then on.
 constexpr int kRkMax = 4096;
-struct RkTable {
-    float v[kRkMax + 1];
+struct alignas(64) RkTable {       // (hi, lo) of 1/k at 2*(k - 1)
+    float v[2 * kRkMax];
     constexpr RkTable() : v{} {
-        for (int k = 1; k <= kRkMax; ++k) v[k] = 1.0f / (float)k;
+        for (int k = 1; k <= kRkMax; ++k) {
+            const float hi = 1.0f / (float)k;
+            v[2 * (k - 1)] = hi;
+            v[2 * (k - 1) + 1] = (float)((1.0 - (double)hi * (double)k) / (double)k);      // (the difference is exact)
+        }
     }
 };
 __device__ const RkTable g_rk{};
+constexpr float kRkMinDev = 0x1p-98f;  // smallest nonzero deviation for which the two-step quotient is proven
 
 constexpr float kLnGuard = 0x1p-21f;   // unit of the guard that lets a guessed level stand without the comparator
-constexpr int kLnRows = 64;       // rows per workgroup (one lane each in phase 1)
-constexpr int kLnThreads = 256;   // threads per workgroup: all four waves work in phase 2
-constexpr int kLnWaves = kLnThreads / 64;
+constexpr int kLnWaves = 7, kLnLoaders = 4;   // waves per workgroup: walker, accumulator, checker and the loading ones
+constexpr int kLnCols = 32;            // columns per chunk (128 bytes of a row)
+constexpr int kDepth = 3;              // chunks a loading wave holds in registers (in flight) ahead of LDS
+constexpr int kXBufs = 4, kMBufs = 2;  // chunks of rows / of running means in LDS
+enum LnMode { kLnVec = 0, kLnRes = 1, kLnScalar = 2 };       // 16-byte loads without / with residual or sum; element loads
 
-template <bool VEC, int SB>
-__global__ __launch_bounds__(kLnThreads) void layernorm_quantize_kernel(LnParams p) {
-    __shared__ float s_mu[kLnRows], s_v[kLnRows], s_rs[kLnRows];
-    const int tid = threadIdx.x;
-    const int64_t row0 = (int64_t)blockIdx.x * kLnRows;
+// The definition's own walk of one row (division), for rows outside the fast step's range.
+__device__ __forceinline__ float2 ln_walk_row(const float *xr, const float *rr, int cols) {
+    float mu = 0.0f, m2 = 0.0f;
+#pragma unroll 2
+    for (int j = 0; j < cols; ++j) {
+        float t = xr[j];
+        if (rr) t = t + rr[j];
+        const float d1 = t - mu;
+        mu = mu + d1 / (float)(j + 1);
+        const float d2 = t - mu;
+        const float pr = d1 * d2;
+        m2 = m2 + pr;
+    }
+    return make_float2(mu, m2);
+}
+
+// R rows per workgroup: see layernorm_quantize_launch.
+// A chunk in LDS: 16-byte group c (four columns) of row r at c * (R + 1) + r, so that a wave reads one group of
+// its rows contiguously, at offsets from one base that are compile-time constants.
+template <int MODE, int SB, int R>
+__global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(LnParams p) {
+    constexpr int CH = kLnCols, NW = kLnWaves, LW = kLnLoaders;
+    constexpr int kGroups = CH / 4, CQ = kGroups * (R + 1);
+    constexpr bool VEC = MODE != kLnScalar;
+    static_assert(NW == 3 + LW && R <= 64 && CH % 16 == 0 && kRkMax % CH == 0, "roles");
+    __shared__ __attribute__((aligned(16))) float4 s_ln[(kXBufs + kMBufs) * CQ];
+    float4 *s_x = s_ln;                                   // [kXBufs] chunks of rows
+    float4 *s_m = s_ln + kXBufs * CQ;                     // [kMBufs] chunks of running means
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t row0 = (int64_t)blockIdx.x * R;
     const int cols = (int)p.cols;
     const float nf = (float)cols;
 
     // ---- phase 1: Eq. 5, mu_i = mu_{i-1} + (x_i - mu_{i-1}) / i,
     //                     M_i  = M_{i-1}  + (x_i - mu_{i-1}) * (x_i - mu_i)
-    // The wave that walks the rows rotates with the workgroup index, so that the workgroups
-    // sharing a CU keep different SIMDs busy with their recurrences.
-    const int p1 = tid - (int)(blockIdx.x % kLnWaves) * 64;        // row of this lane in phase 1, if in [0, 64)
-    if (p1 >= 0 && p1 < kLnRows && row0 + p1 < p.rows) {
-        const float *xr = p.x + (row0 + p1) * p.ld;
-        const float *rr = p.res ? p.res + (row0 + p1) * p.ld : nullptr;
-        float mu = 0.0f, m2 = 0.0f;
-        // One pass over the row.  FAST replaces the IEEE division d1 / i by the two-FMA correction
-        // of d1 * RN(1/i) (see g_rk), which gives the same bits whenever d1 is zero or an ordinary
-        // finite number: the pass tracks the largest and the smallest nonzero |d1| and reports
-        // whether that held; the caller repeats the row with the division otherwise.
-        auto walk = [&](auto FAST_T) -> bool {
-            constexpr bool FAST = decltype(FAST_T)::value;
-            mu = 0.0f; m2 = 0.0f;
-            float hi = 0.0f, lo = 1.0f;
-            auto step1 = [&](float xi, int i1) {      // i1 = 1-based index of the element
-                const float d1 = xi - mu;
-                float q;
-                if constexpr (FAST) {
-                    const float kf = (float)i1, rk = g_rk.v[i1];
-                    const float q0 = d1 * rk;
-                    const float r = fmaf(-q0, kf, d1);
-                    q = fmaf(r, rk, q0);
-                    hi = fmaxf(hi, fabsf(d1));
-                    lo = fminf(lo, d1 == 0.0f ? 1.0f : fabsf(d1));
-                } else {
-                    q = d1 / (float)i1;
+    // The roles rotate with the workgroup index (of the workgroups of one XCD, which arrive at a CU in
+    // steps of its 32 CUs), so that the workgroups sharing a CU walk their rows on different SIMDs.
+    const int role = (int)(((u32)wave + (blockIdx.x >> 3) + (blockIdx.x >> 8)) % (u32)NW);
+    const int nch = (cols + CH - 1) / CH;
+    const int lr = min(lane, R - 1);
+    float mu = 0.0f, m2 = 0.0f;
+    u32 least = 0xFFFFFFFFu;                              // bits of the smallest nonzero deviation, minus one
+    // Step t, between two barriers: chunk t is walked, chunk t - 1 accumulated and checked, chunk t + 2 put
+    // into LDS (chunk t + 1 is there: the walker fetches it into registers as it consumes chunk t).  Every
+    // role passes the same nch + 2 barriers.
+    if (role == 0) {
+        __syncthreads();
+        float4 x[kGroups];
+#pragma unroll
+        for (int c = 0; c < kGroups; ++c) x[c] = s_x[c * (R + 1) + lr];
+        typedef __attribute__((address_space(4))) const v16f const_v16f;      // (constant memory: scalar loads)
+        uint64_t rk = reinterpret_cast<uint64_t>(g_rk.v);
+        asm("" : "+s"(rk));                               // (one address computation, not one per load)
+        v16f k16[CH / 8];
+        auto load_rk = [&](int g, int t) {                // (a chunk beyond the table divides instead)
+            k16[g] = reinterpret_cast<const_v16f *>(rk)[(CH / 8) * min(t, kRkMax / CH - 1) + g];
+        };
+#pragma unroll
+        for (int g = 0; g < CH / 8; ++g) load_rk(g, 0);
+        for (int t = 0; t <= nch; ++t) {
+            if (t < nch) {
+                const float4 *next = s_x + ((t + 1) % kXBufs) * CQ + lr;
+                float4 *dst = s_m + (t % kMBufs) * CQ + lr;
+                const int n = min(cols - t * CH, CH);
+                if (n == CH && (t + 1) * CH <= kRkMax) {
+#pragma unroll
+                    for (int c = 0; c < kGroups; ++c) {
+                        auto step = [&](float xv, int i) {
+                            const float d1 = xv - mu;
+                            const float tq = d1 * k16[c >> 1][8 * (c & 1) + 2 * i + 1];
+                            mu = mu + fmaf(d1, k16[c >> 1][8 * (c & 1) + 2 * i], tq);
+                            return mu;
+                        };
+                        float4 m;
+                        m.x = step(x[c].x, 0); m.y = step(x[c].y, 1); m.z = step(x[c].z, 2); m.w = step(x[c].w, 3);
+                        __builtin_amdgcn_sched_barrier(0);
+                        dst[c * (R + 1)] = m;
+                        x[c] = next[c * (R + 1)];
+                        if (c & 1) load_rk(c >> 1, t + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                } else {                                  // a last partial chunk, or one beyond the table
+                    const float *xs = reinterpret_cast<const float *>(s_x + (t % kXBufs) * CQ + lr);
+                    for (int i = 0; i < n; ++i) {
+                        const float xv = xs[(i >> 2) * 4 * (R + 1) + (i & 3)];
+                        const float d1 = xv - mu;
+                        mu = mu + d1 / (float)(t * CH + i + 1);
+                        reinterpret_cast<float *>(dst)[(i >> 2) * 4 * (R + 1) + (i & 3)] = mu;
+                    }
+#pragma unroll
+                    for (int c = 0; c < kGroups; ++c) x[c] = next[c * (R + 1)];
                 }
-                mu = mu + q;
-                const float d2 = xi - mu;
+            }
+            __syncthreads();
+        }
+    } else if (role == 1 || role == 2) {
+        auto run = [&](auto &&f) {
+            __syncthreads();
+            __syncthreads();
+            for (int t = 0; t < nch; ++t) {
+                const float4 *src = s_x + (t % kXBufs) * CQ + lr;
+                const float4 *msrc = s_m + (t % kMBufs) * CQ + lr;
+                const int n = min(cols - t * CH, CH);
+                if (n == CH) {
+#pragma unroll
+                    for (int c = 0; c < kGroups; ++c) {
+                        const float4 x = src[c * (R + 1)], m = msrc[c * (R + 1)];
+                        f(x.x, m.x); f(x.y, m.y); f(x.z, m.z); f(x.w, m.w);
+                    }
+                } else {
+                    for (int i = 0; i < n; ++i)
+                        f(reinterpret_cast<const float *>(src)[(i >> 2) * 4 * (R + 1) + (i & 3)],
+                          reinterpret_cast<const float *>(msrc)[(i >> 2) * 4 * (R + 1) + (i & 3)]);
+                }
+                __syncthreads();
+            }
+        };
+        if (role == 1)
+            run([&](float x, float m) {
+                const float d1 = x - mu;                  // (mu: the mean before this element)
+                const float d2 = x - m;
                 const float pr = d1 * d2;
                 m2 = m2 + pr;
-            };
-            int j = 0;
-            if (VEC) {
-                constexpr int CH = VITQ_LN_CH;
-                const int full = cols / CH * CH;
-                auto load_chunk = [&](int j0, float (&v)[CH]) {
+                mu = m;
+            });
+        else
+            run([&](float x, float m) {
+                const float d1 = x - mu;                  // (zero wraps to the largest value)
+                least = min(least, (__float_as_uint(d1) & 0x7FFFFFFFu) - 1u);
+                mu = m;
+            });
+    } else {
+        // loading waves: each lane brings one or two 16-byte groups of a chunk (chunks of 128-byte row pieces)
+        constexpr int ITEMS = R * kGroups, LT = LW * 64, IT = (ITEMS + LT - 1) / LT;
+        static_assert(ITEMS % LT == 0 || IT == 1, "items of the loading waves");
+        const int lt = (role - 3) * 64 + lane;
+        const bool loader = role < 3 + LW && (role - 3) * 64 < ITEMS;      // (wave-uniform)
+        // Rows and columns beyond the matrix are clamped (what they bring is never used): unconditional loads
+        // keep the compiler's count of what is in flight, so that a put waits for its own chunk only.
+        struct Piece { float4 x[IT], r[MODE == kLnRes ? IT : 1]; };
+        int64_t at[IT];
 #pragma unroll
-                    for (int q = 0; q < CH / 4; ++q) {
-                        float4 a = *reinterpret_cast<const float4 *>(xr + j0 + 4 * q);
-                        if (rr) {
-                            const float4 b = *reinterpret_cast<const float4 *>(rr + j0 + 4 * q);
-                            a.x = a.x + b.x; a.y = a.y + b.y; a.z = a.z + b.z; a.w = a.w + b.w;
-                        }
-                        v[4 * q] = a.x; v[4 * q + 1] = a.y; v[4 * q + 2] = a.z; v[4 * q + 3] = a.w;
+        for (int it = 0; it < IT; ++it)
+            at[it] = min(row0 + (it * LT + lt) / kGroups, p.rows - 1) * p.ld;
+        auto fetch = [&](int ch, Piece &v) {
+            const int c = min(ch, nch - 1) * CH + 4 * (lt % kGroups);
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                if constexpr (MODE == kLnScalar) {
+                    float e[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int64_t i = at[it] + min(c + j, cols - 1);
+                        e[j] = p.res ? p.x[i] + p.res[i] : p.x[i];
                     }
-                };
-                if (full > 0) {
-                    float cur[CH], nxt[CH];
-                    load_chunk(0, cur);
-                    for (; j < full; j += CH) {
-                        load_chunk(min(j + CH, full - CH), nxt);      // (the last one re-reads its own chunk: no branch)
-#pragma unroll
-                        for (int i = 0; i < CH; ++i) step1(cur[i], j + i + 1);
-#pragma unroll
-                        for (int i = 0; i < CH; ++i) cur[i] = nxt[i];
-                    }
+                    v.x[it] = make_float4(e[0], e[1], e[2], e[3]);
+                } else {
+                    const int64_t i = at[it] + min(c, cols - 4);
+                    v.x[it] = *reinterpret_cast<const float4 *>(p.x + i);
+                    if constexpr (MODE == kLnRes) v.r[it] = *reinterpret_cast<const float4 *>((p.res ? p.res : p.x) + i);
                 }
             }
-            for (; j < cols; ++j) {                   // ragged tail, unaligned rows
-                float t = xr[j];
-                if (rr) t = t + rr[j];
-                step1(t, j + 1);
-            }
-            // (a NaN deviation is skipped by the max but makes mu NaN; an infinite one shows in hi)
-            return !FAST || (hi <= 0x1p120f && lo >= 0x1p-100f && mu == mu);
         };
-        bool done = false;
-        if (cols <= kRkMax) done = walk(std::true_type{});
-        if (!done) walk(std::false_type{});
+        auto put = [&](int ch, const Piece &v) {
+            float4 *dst = s_x + (ch % kXBufs) * CQ;
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                const int i = it * LT + lt;
+                float4 a = v.x[it];
+                if (MODE == kLnRes && p.res) {
+                    a.x = a.x + v.r[it].x; a.y = a.y + v.r[it].y; a.z = a.z + v.r[it].z; a.w = a.w + v.r[it].w;
+                }
+                dst[(i % kGroups) * (R + 1) + i / kGroups] = a;
+            }
+        };
+        if (loader) {
+            Piece pre[kDepth];
+            static_for<kDepth>([&](auto D) { fetch(decltype(D)::value, pre[decltype(D)::value]); });
+            put(0, pre[0]);
+            fetch(kDepth, pre[0]);
+            put(1, pre[1]);
+            fetch(kDepth + 1, pre[1]);
+            __syncthreads();
+            // step t stores chunk t + 2, held in pre[(t + 2) % kDepth] (past the last chunk: into a free buffer)
+            int t = 0;
+            for (; t + kDepth <= nch + 1; t += kDepth)
+                static_for<kDepth>([&](auto D) {
+                    constexpr int d = decltype(D)::value, slot = (d + 2) % kDepth;
+                    put(t + d + 2, pre[slot]);
+                    fetch(t + d + 2 + kDepth, pre[slot]);
+                    __syncthreads();
+                });
+            static_for<kDepth - 1>([&](auto D) {
+                constexpr int d = decltype(D)::value, slot = (d + 2) % kDepth;
+                if (t + d <= nch) {
+                    put(t + d + 2, pre[slot]);
+                    __syncthreads();
+                }
+            });
+        } else {
+            for (int t = 0; t < nch + 2; ++t) __syncthreads();
+        }
+    }
+    // ---- phase 2: levels.  A pass covers BL blocks of 256 columns: lane l owns columns c0..c0+3 of each, a
+    // wave every NW-th row; a pass's loads go out together, the first pass's before the statistics are
+    // exchanged. ----
+    constexpr int ROWS = (R + NW - 1) / NW;               // rows of a wave
+    constexpr int HALVES = (ROWS + 3) / 4;                // (many rows: a part of them per pass)
+    constexpr int NB = (ROWS + HALVES - 1) / HALVES;      // of them per pass
+    constexpr int BL = NB <= 3 ? 2 : 1;
+    const int nrows = (int)min((int64_t)R, p.rows - row0);
+    const int padded = p.row_bytes16 * 8 / SB;            // columns of the 16-byte padded row
+    float4 xv[BL][NB], gv[BL], bv[BL];
+    auto row_of = [&](int pass, int k) { return wave + NW * (k + NB * (pass % HALVES)); };
+    auto element = [&](int64_t at, int c) {
+        float t = p.x[at + c];
+        if (p.res) t = t + p.res[at + c];
+        return t;
+    };
+    // 16 bytes at a uniform base plus a 32-bit lane offset
+    auto load4 = [](const float *base, u32 off) {
+        return *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(base) + off);
+    };
+    auto load_pass = [&](int pass) {                      // (columns and rows beyond the matrix: clamped, not used)
+        int64_t at[NB];
+        int r = min(row_of(pass, 0), nrows - 1);
+        at[0] = (row0 + r) * p.ld;
+#pragma unroll
+        for (int k = 1; k < NB; ++k) {
+            const bool more = r + NW < nrows;
+            at[k] = at[k - 1] + (more ? NW * p.ld : 0);
+            r += more ? NW : 0;
+        }
+#pragma unroll
+        for (int bl = 0; bl < BL; ++bl) {
+            const int c0 = 4 * lane + 256 * (pass / HALVES * BL + bl);
+            [[maybe_unused]] const int c[4] = {min(c0, cols - 1), min(c0 + 1, cols - 1), min(c0 + 2, cols - 1), min(c0 + 3, cols - 1)};
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                float4 &v = xv[bl][k];
+                if constexpr (VEC) {
+                    const u32 cv = 4u * (u32)min(c0, cols - 4);
+                    v = load4(p.x + at[k], cv);
+                    if constexpr (MODE == kLnRes) {
+                        if (p.res) {
+                            const float4 r4 = load4(p.res + at[k], cv);
+                            v.x = v.x + r4.x; v.y = v.y + r4.y; v.z = v.z + r4.z; v.w = v.w + r4.w;
+                        }
+                    }
+                } else {
+                    v = make_float4(element(at[k], c[0]), element(at[k], c[1]), element(at[k], c[2]), element(at[k], c[3]));
+                }
+            }
+            if constexpr (VEC) {
+                gv[bl] = load4(p.gamma, 4u * (u32)min(c0, cols - 4));
+                bv[bl] = load4(p.beta, 4u * (u32)min(c0, cols - 4));
+            } else {
+                gv[bl] = make_float4(p.gamma[c[0]], p.gamma[c[1]], p.gamma[c[2]], p.gamma[c[3]]);
+                bv[bl] = make_float4(p.beta[c[0]], p.beta[c[1]], p.beta[c[2]], p.beta[c[3]]);
+            }
+        }
+    };
+    load_pass(0);
+
+    // the chunks are done with: their LDS holds the statistics from here on
+    float4 *s_row = s_ln;                                 // [R] mean, guess of 1/(sigma*step), 0 (or infinity: no guess), V
+    float *s_m2 = reinterpret_cast<float *>(s_ln + R);    // [R] sum of squared deviations
+    u32 *s_least = reinterpret_cast<u32 *>(s_m2 + R);
+    if (lane < R) {
+        if (role == 1) s_m2[lane] = m2;
+        else if (role == 2) s_least[lane] = least;
+    }
+    __syncthreads();
+    const float rstep = __builtin_amdgcn_rcpf(p.step);    // for the guess only
+    if (role == 0 && lane < nrows) {
+        m2 = s_m2[lane];
+        // (a deviation too small for the two-step quotient, or anything that is not finite: divide)
+        const bool ok = fabsf(mu) <= 3.0e38f && s_least[lane] >= __float_as_uint(kRkMinDev) - 1u;
+        if (!ok) {
+            const float2 st = ln_walk_row(p.x + (row0 + lane) * p.ld, p.res ? p.res + (row0 + lane) * p.ld : nullptr, cols);
+            mu = st.x;
+            m2 = st.y;
+        }
         const float ne = nf * p.eps;
         const float V = m2 + ne;
-        s_mu[p1] = mu;
-        s_v[p1] = V;
-        s_rs[p1] = __builtin_amdgcn_rsqf(V / nf);      // for the guess only
+        // in a row whose V is not an ordinary number every element is compared
+        const bool plain = V >= 0x1p-40f && V <= 0x1p30f && p.step >= 0x1p-20f && p.step <= 0x1p10f;
+        s_row[lane] = make_float4(mu, __builtin_amdgcn_rsqf(V / nf) * rstep, plain ? 0.0f : __uint_as_float(0x7F800000u), V);
     }
     __syncthreads();
 
-    // ---- phase 2: levels, one row per wave at a time, four consecutive elements per lane ----
-    const int lane = tid & 63, wave = tid >> 6;
-    const float rstep = __builtin_amdgcn_rcpf(p.step);   // for the guess only
-    const bool step_ok = p.step >= 0x1p-20f && p.step <= 0x1p10f;
+    // The guess.  In exact arithmetic on the fp32 values g, beta, step, V the comparator asks whether
+    // t* = (g / sigma + beta) / step exceeds lv - 1/2 (sigma^2 = V/n).  The value tp computed here with the
+    // hardware rsq / rcp, tp = g * (rs*rstep) + beta*rstep, differs from t* by at most
+    // (|g/(sigma*step)| + |beta/step|) * 2^-21, and the comparator's own fp32 evaluation moves its boundary by at
+    // most (2|lv| + |beta/step| + 1) * 2^-22 (five roundings on the two sides, two of them doubled by the
+    // squares).  So when tp is further than kLnGuard * (4|tp| + 3|beta/step| + 3) from every half-integer, the
+    // rounded tp is the level the comparator would count, and the comparator is not run.  With at most 4-bit
+    // fields |tp| is taken as 8.5, which holds wherever a boundary is near (beyond it the level is the clamp on
+    // both sides), and the bias -qmin rides in the FMA's addend (two more roundings of values below 16: 2
+    // units); with 8-bit fields the lane's largest |tp| is used.  (A NaN tp drops out of the maxima, but then the
+    // row's guess is marked infinite, or a gamma or beta is not finite and the limit is NaN.)
+    // The relative-error model behind these bounds needs the squares to stay
+    // ordinary numbers: the guess is trusted only for 2^-20 <= step <= 2^10 and 2^-40 <= V <= 2^30 (then an
+    // underflowing g*|g| can differ from the exact product by 2^-139 at most, against
+    // |L - R| >= V * step^2 * d^2 for a value d levels from a boundary, and nothing overflows below the |tp|
+    // that the guard itself rejects).
     const float qminf = (float)p.qmin, qmaxf = (float)p.qmax;
-    const int span = p.qmax - p.qmin;
-    const int padded = p.row_bytes16 * 8 / SB;           // columns of the 16-byte padded row
-    for (int c0 = 4 * lane; c0 < padded; c0 += 256) {
-        // this lane's four columns are the same for every row
-        float gm[4], bt[4], cg[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const bool ok = c0 + i < cols;
-            gm[i] = ok ? p.gamma[c0 + i] : 0.0f;
-            bt[i] = ok ? p.beta[c0 + i] : 0.0f;
-            cg[i] = fmaf(fabsf(bt[i] * rstep), 3.0f * kLnGuard, 3.0f * kLnGuard);   // the guess's guard, constant part
+    const float top = qmaxf - qminf;
+    const u32 unbias = (u32)(p.qmin & ((1 << SB) - 1)) * 0x01010101u;    // added per byte: level - qmin -> field
+    [[maybe_unused]] auto d8 = [&](float t) { return rintf(t) - qminf; };      // (rounded first: adding the bias would round again)
+    // packs the four levels (one byte each, biased by -qmin) of columns c0.. of a row and stores them
+    uint8_t *const out0 = p.out + row0 * p.out_stride;
+    const u32 ostride = (u32)p.out_stride;
+    auto store_levels = [&](int r, int c0, u32 w) {
+        uint8_t *dst = out0 + (u32)r * (uint64_t)ostride + (u32)(c0 * SB / 8);
+        if constexpr (SB == 8) w = ((w & 0x7F7F7F7Fu) + (unbias & 0x7F7F7F7Fu)) ^ ((w ^ unbias) & 0x80808080u);
+        else w = (w + unbias) & (((1u << SB) - 1u) * 0x01010101u);
+        if (padded != cols) {                             // zeros beyond the last column
+            const int live = cols - c0;
+            if (live < 4) w &= live <= 0 ? 0u : ((1u << (8 * live)) - 1u);
         }
-        // Rows are taken in batches of RB; the loads of the next batch are in flight while the
-        // current one is decided (the rows no longer sit in a near cache after phase 1).
-        constexpr int RB = VITQ_LN_RB, NB = kLnRows / kLnWaves / RB;
-        auto load_batch = [&](int bi, float (&v)[RB][4]) {
+        if constexpr (SB == 8) *reinterpret_cast<u32 *>(dst) = w;
+        else if constexpr (SB == 4)
+            *reinterpret_cast<uint16_t *>(dst) = (uint16_t)__builtin_amdgcn_perm(0u, w | (w >> 4), 0x0C0C0200u);
+        else *dst = (uint8_t)(w | (w >> 6) | (w >> 12) | (w >> 18));
+    };
+    for (int pass = 0; pass / HALVES * BL * 256 < padded; ++pass) {
+        if (pass > 0) load_pass(pass);
+        u32 redo = 0;                                     // (wave-uniform) items to be decided by the comparator
+        static_for<BL>([&](auto BLK) {
+            constexpr int bl = decltype(BLK)::value;
+            const int c0 = 4 * lane + 256 * (pass / HALVES * BL + bl);
+            if (c0 >= padded) return;
+            const float gm[4] = {gv[bl].x, gv[bl].y, gv[bl].z, gv[bl].w}, bt[4] = {bv[bl].x, bv[bl].y, bv[bl].z, bv[bl].w};
+            float btr[4], bmax = 0.0f, odd = 0.0f;
 #pragma unroll
-            for (int k = 0; k < RB; ++k) {
-                const int r = wave + kLnWaves * (bi * RB + k);
-                const int64_t row = row0 + r;
-                v[k][0] = v[k][1] = v[k][2] = v[k][3] = 0.0f;
-                if (row < p.rows) {
-                    const float *xr = p.x + row * p.ld;
-                    if (VEC && c0 + 4 <= cols) {
-                        float4 a = *reinterpret_cast<const float4 *>(xr + c0);
-                        if (p.res) {
-                            const float4 b = *reinterpret_cast<const float4 *>(p.res + row * p.ld + c0);
-                            a.x = a.x + b.x; a.y = a.y + b.y; a.z = a.z + b.z; a.w = a.w + b.w;
-                        }
-                        v[k][0] = a.x; v[k][1] = a.y; v[k][2] = a.z; v[k][3] = a.w;
-                        if (p.sum_out) *reinterpret_cast<float4 *>(p.sum_out + row * p.ld + c0) = a;
-                    } else {
+            for (int i = 0; i < 4; ++i) {
+                btr[i] = SB == 8 ? bt[i] * rstep : fmaf(bt[i], rstep, -qminf);
+                bmax = fmaxf(bmax, fabsf(bt[i] * rstep));
+                odd = odd + (gm[i] - gm[i]) + (bt[i] - bt[i]);           // NaN unless all of them are finite
+            }
+            const float limit = (0.5f - kLnGuard * (3.0f * bmax + (SB == 8 ? 3.0f : 39.0f))) + odd;
+            static_for<NB>([&](auto K) {
+                constexpr int k = decltype(K)::value;
+                const int r = row_of(pass, k);
+                __builtin_amdgcn_sched_barrier(0);        // (items in turn: bounds the registers)
+                if (r < nrows) {
+                    const float x[4] = {xv[bl][k].x, xv[bl][k].y, xv[bl][k].z, xv[bl][k].w};
+                    const float4 st = s_row[r];
+                    float tp[4], d[4];
+                    u32 w = 0;
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            if (c0 + i < cols) {
-                                float t = xr[c0 + i];
-                                if (p.res) t = t + p.res[row * p.ld + c0 + i];
-                                if (p.sum_out) p.sum_out[row * p.ld + c0 + i] = t;
-                                v[k][i] = t;
+                    for (int i = 0; i < 4; ++i) {
+                        const float a = x[i] - st.x;
+                        const float g = a * gm[i];
+                        tp[i] = fmaf(g, st.y, btr[i]);
+                        d[i] = tp[i] - rintf(tp[i]);
+                        // (to nearest even, saturates to a byte)
+                        const float lv = SB == 8 ? fminf(d8(tp[i]), top) : __builtin_amdgcn_fmed3f(tp[i], 0.0f, top);
+                        w = __builtin_amdgcn_cvt_pk_u8_f32(lv, i, w);
+                    }
+                    const float far = fmaxf(fmaxf(fmaxf(fabsf(d[0]), fabsf(d[1])), fabsf(d[2])), fabsf(d[3]));
+                    float fig = far + st.z;
+                    if constexpr (SB == 8)
+                        fig = fmaf(fmaxf(fmaxf(fmaxf(fabsf(tp[0]), fabsf(tp[1])), fabsf(tp[2])), fabsf(tp[3])), 4.0f * kLnGuard, fig);
+                    if (__builtin_amdgcn_ballot_w64(!(fig <= limit)) != 0) redo |= 1u << (bl * NB + k);
+                    store_levels(r, c0, w);
+                    if constexpr (MODE != kLnVec) {
+                        if (p.sum_out) {
+                            float *so = p.sum_out + (row0 + r) * p.ld + c0;
+                            if constexpr (VEC) {
+                                if (c0 < cols) *reinterpret_cast<float4 *>(so) = xv[bl][k];
+                            } else {
+#pragma unroll
+                                for (int i = 0; i < 4; ++i)
+                                    if (c0 + i < cols) so[i] = x[i];
                             }
                         }
                     }
                 }
+            });
+        });
+        // Rare: items with an element inside the guard.  level = qmin + #{lv : above(lv)}; above() is monotone in
+        // lv, so c is the level iff above(c) (or c == qmin) and not above(c + 1) (or c == qmax).
+        while (redo) {
+            const int item = __builtin_ctz(redo);
+            redo &= redo - 1;
+            const int c0 = 4 * lane + 256 * (pass / HALVES * BL + item / NB), r = row_of(pass, item % NB);
+            if (c0 >= padded) continue;
+            const float4 st = s_row[r];
+            const float V = st.w;
+            const int c[4] = {c0, min(c0 + 1, cols - 1), min(c0 + 2, cols - 1), min(c0 + 3, cols - 1)};
+            float L[4], bt[4], lv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int64_t at = (row0 + r) * p.ld + min(c[i], cols - 1);
+                const float x = MODE != kLnVec && p.sum_out ? p.sum_out[at] : (p.res ? p.x[at] + p.res[at] : p.x[at]);
+                const float a = x - st.x;
+                const float g = a * p.gamma[min(c[i], cols - 1)];
+                bt[i] = p.beta[min(c[i], cols - 1)];
+                const float gs = g * fabsf(g);
+                L[i] = gs * nf;
+                lv[i] = fminf(fmaxf(rintf(fmaf(g, st.y, bt[i] * rstep)), qminf), qmaxf);             // (NaN: qmin)
             }
-        };
-        float cur[RB][4], nxt[RB][4];
-        load_batch(0, cur);
-        for (int bi = 0; bi < NB; ++bi) {
-            if (row0 + wave + kLnWaves * (bi * RB) >= p.rows) break;      // no rows left for this wave
-            if (bi + 1 < NB) load_batch(bi + 1, nxt);
-            // The guess.  In exact arithmetic on the fp32 values g, beta, step, V the comparator asks whether
-            // t* = (g / sigma + beta) / step exceeds lv - 1/2 (sigma^2 = V/n).  The value tp computed here with
-            // the hardware rsq / rcp differs from t* by at most (|g/(sigma*step)| + |beta/step|) * 2^-21, and
-            // the comparator's own fp32 evaluation moves its boundary by at most (2|lv| + |beta/step| + 1) *
-            // 2^-22 (five roundings on the two sides, two of them doubled by the squares).  So when tp is
-            // further than kLnGuard * (4|tp| + 3|beta/step| + 3) from every half-integer, rint(tp) is the level
-            // the comparator would count, and the comparator is not run; a NaN or an infinity makes the
-            // figure NaN, which compares above the limit as a bit pattern.  The relative-error model behind
-            // these bounds needs the squares to stay ordinary numbers: the guess is trusted only for
-            // 2^-20 <= step <= 2^10 and 2^-40 <= V <= 2^30 (then an underflowing g*|g| can differ from the
-            // exact product by 2^-139 at most, against |L - R| >= V * step^2 * d^2 for a value d levels from a
-            // boundary, and nothing overflows below the |tp| that the guard itself rejects).
-            float L[RB][4], c[RB][4], V[RB];
-            u32 worst = step_ok ? 0u : 0x7FC00000u;
-#pragma unroll
-            for (int k = 0; k < RB; ++k) {
-                const int r = wave + kLnWaves * (bi * RB + k);
-                const float mu = s_mu[r], rs = s_rs[r];
-                V[k] = s_v[r];
-                if (!(V[k] >= 0x1p-40f && V[k] <= 0x1p30f)) worst = 0x7FC00000u;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float a = cur[k][i] - mu;
-                    const float g = a * gm[i];
-                    const float tp = fmaf(g, rs, bt[i]) * rstep;
-                    const float t = rintf(tp);
-                    const float fig = fmaf(fabsf(tp), 4.0f * kLnGuard, fabsf(tp - t)) + cg[i];
-                    worst = max(worst, __float_as_uint(fig));
-                    c[k][i] = (t == t) ? __builtin_amdgcn_fmed3f(t, qminf, qmaxf) : qminf;
-                }
-            }
-            const bool verify = __builtin_amdgcn_ballot_w64(worst > __float_as_uint(0.5f)) != 0;
-            if (verify) {
-#pragma unroll
-                for (int k = 0; k < RB; ++k) {
-                    const float mu = s_mu[wave + kLnWaves * (bi * RB + k)];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float a = cur[k][i] - mu;
-                        const float g = a * gm[i];
-                        const float gs = g * fabsf(g);
-                        L[k][i] = gs * nf;
-                    }
-                }
-            }
-            // comparator of Fig. 5(b): element (k, i) against the reference (lv - 1/2)*step
-            auto above = [&](int k, int i, float lv) {
-                const float rk = (lv - 0.5f) * p.step;
+            auto above = [&](int i, float k) {            // comparator of Fig. 5(b)
+                const float rk = (k - 0.5f) * p.step;
                 const float cc = rk - bt[i];
                 const float cs = cc * fabsf(cc);
-                const float R = cs * V[k];
-                return L[k][i] > R;
+                const float rhs = cs * V;
+                return L[i] > rhs;
             };
-            // level = qmin + #{lv : above(lv)}; above() is monotone in lv, so c is the level iff
-            // above(c) (or c == qmin) and not above(c + 1) (or c == qmax)
-            for (int it = 0; verify && it <= span; ++it) {
+            for (int it = 0; it <= p.qmax - p.qmin; ++it) {
                 bool moved = false;
 #pragma unroll
-                for (int k = 0; k < RB; ++k)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const bool low_ok = (c[k][i] <= qminf) || above(k, i, c[k][i]);
-                        const bool high_ok = (c[k][i] >= qmaxf) || !above(k, i, c[k][i] + 1.0f);
-                        const float d = !low_ok ? -1.0f : (!high_ok ? 1.0f : 0.0f);
-                        c[k][i] = c[k][i] + d;
-                        moved = moved || (d != 0.0f);
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    const bool low_ok = (lv[i] <= qminf) || above(i, lv[i]);
+                    const bool high_ok = (lv[i] >= qmaxf) || !above(i, lv[i] + 1.0f);
+                    const float d = !low_ok ? -1.0f : (!high_ok ? 1.0f : 0.0f);
+                    lv[i] = lv[i] + d;
+                    moved = moved || d != 0.0f;
+                }
                 if (__builtin_amdgcn_ballot_w64(moved) == 0) break;
             }
+            u32 w = 0;
 #pragma unroll
-            for (int k = 0; k < RB; ++k) {
-                const int64_t row = row0 + wave + kLnWaves * (bi * RB + k);
-                if (row < p.rows) {
-                    u32 w = 0;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const u32 field = (c0 + i < cols) ? ((u32)(int)c[k][i] & ((1u << SB) - 1u)) : 0u;
-                        w |= field << (i * SB);
-                    }
-                    uint8_t *dst = p.out + row * p.out_stride + (int64_t)c0 * SB / 8;
-                    if constexpr (SB == 8) *reinterpret_cast<u32 *>(dst) = w;
-                    else if constexpr (SB == 4) *reinterpret_cast<uint16_t *>(dst) = (uint16_t)w;
-                    else *dst = (uint8_t)w;
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < RB; ++k)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) cur[k][i] = nxt[k][i];
+            for (int i = 0; i < 4; ++i) w |= (u32)(int)(lv[i] - qminf) << (8 * i);
+            store_levels(r, c0, w);
         }
     }
 }
@@ -402,14 +610,31 @@ hipError_t qkv_headnorm_launch(const HeadNormParams &p, hipStream_t stream) {
 hipError_t layernorm_quantize_launch(const LnParams &p, hipStream_t stream) {
     if (p.rows == 0) return hipSuccess;
     const bool vec = (p.cols % 4 == 0) && (p.ld % 4 == 0) && (((uintptr_t)p.x) % 16 == 0) &&
+                     ((uintptr_t)p.gamma) % 16 == 0 && ((uintptr_t)p.beta) % 16 == 0 &&
                      (!p.res || ((uintptr_t)p.res) % 16 == 0) && (!p.sum_out || ((uintptr_t)p.sum_out) % 16 == 0);
-    const unsigned blocks = (unsigned)((p.rows + kLnRows - 1) / kLnRows);
-#define VITQ_LN_LAUNCH(V, S) hipLaunchKernelGGL((layernorm_quantize_kernel<V, S>), dim3(blocks), dim3(kLnThreads), 0, stream, p)
-    if (p.sb == 4) { if (vec) VITQ_LN_LAUNCH(true, 4); else VITQ_LN_LAUNCH(false, 4); }
-    else if (p.sb == 8) { if (vec) VITQ_LN_LAUNCH(true, 8); else VITQ_LN_LAUNCH(false, 8); }
-    else if (p.sb == 2) { if (vec) VITQ_LN_LAUNCH(true, 2); else VITQ_LN_LAUNCH(false, 2); }
+    // Rows per workgroup.  The recurrences take the same time for 16 rows as for 64 (a lane is a row); fewer rows
+    // leave a wave fewer of them in the level pass and bring more CUs in, as long as every workgroup is resident:
+    // three per CU (80 registers, 21 waves), so 12,288 and 24,576 rows are where one more round would begin.
+    // Measured (768 columns, us; one lane per row with the division-sized step on one wave -> this kernel):
+    // 197 rows 50 -> 19.5, 12,608 rows 59 -> 32, 25,216 rows 64 -> 40, 50,432 rows 76 -> 72, 100,000 rows 154 -> 117.
+    const int64_t slots = 3 * 256;
+    const int R = p.rows <= 16 * slots ? 16 : (p.rows <= 32 * slots ? 32 : 64);
+    const unsigned blocks = (unsigned)((p.rows + R - 1) / R);
+    auto launch = [&](auto M, auto SB) {
+        constexpr int mode = decltype(M)::value, sb = decltype(SB)::value;
+        if (R == 16) hipLaunchKernelGGL((layernorm_quantize_kernel<mode, sb, 16>), dim3(blocks), dim3(kLnWaves * 64), 0, stream, p);
+        else if (R == 32) hipLaunchKernelGGL((layernorm_quantize_kernel<mode, sb, 32>), dim3(blocks), dim3(kLnWaves * 64), 0, stream, p);
+        else hipLaunchKernelGGL((layernorm_quantize_kernel<mode, sb, 64>), dim3(blocks), dim3(kLnWaves * 64), 0, stream, p);
+    };
+    auto launch_mode = [&](auto SB) {
+        if (!vec) launch(std::integral_constant<int, kLnScalar>{}, SB);
+        else if (p.res || p.sum_out) launch(std::integral_constant<int, kLnRes>{}, SB);
+        else launch(std::integral_constant<int, kLnVec>{}, SB);
+    };
+    if (p.sb == 4) launch_mode(std::integral_constant<int, 4>{});
+    else if (p.sb == 8) launch_mode(std::integral_constant<int, 8>{});
+    else if (p.sb == 2) launch_mode(std::integral_constant<int, 2>{});
     else return hipErrorInvalidValue;
-#undef VITQ_LN_LAUNCH
     return hipGetLastError();
 }
 

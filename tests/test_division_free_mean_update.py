@@ -51,3 +51,23 @@ def test_corrected_reciprocal_multiply_equals_ieee_division():
         out = subprocess.run([exe], capture_output=True, text=True)
         n, bad = (int(v) for v in out.stdout.split())
         assert out.returncode == 0 and bad == 0 and n == 4096 * 6000 * 3
+
+
+SRC_TWO_STEP = SRC.replace("const float kf = (float)k, rk = 1.0f / kf;",
+                           "const float kf = (float)k, hi = 1.0f / kf, lo = (float)((1.0 - (double)hi * k) / k);") \
+    .replace("const float q0 = d * rk;", "const float t = d * lo;") \
+    .replace("const float r = fmaf(-q0, kf, d);", "") \
+    .replace("const float q = fmaf(r, rk, q0);", "const float q = fmaf(d, hi, t);")
+
+
+def test_two_step_quotient_equals_ieee_division():
+    """The form the kernel runs: 1/i as a sum hi + lo of two fp32 numbers, t = RN(d*lo), q = RN(d*hi + t)."""
+    assert "fmaf(d, hi, t)" in SRC_TWO_STEP and "rk" not in SRC_TWO_STEP
+    with tempfile.TemporaryDirectory() as d:
+        src, exe = os.path.join(d, "chk.c"), os.path.join(d, "chk")
+        with open(src, "w") as f:
+            f.write(SRC_TWO_STEP)
+        subprocess.run(["gcc", "-O2", "-ffp-contract=off", "-march=native", src, "-o", exe, "-lm"], check=True)
+        out = subprocess.run([exe], capture_output=True, text=True)
+        n, bad = (int(v) for v in out.stdout.split())
+        assert out.returncode == 0 and bad == 0 and n == 4096 * 6000 * 3

@@ -166,3 +166,31 @@ def test_values_planted_on_both_sides_of_every_guard_band(bits, gsign):
         delta = float(rng.choice([-1.0, 1.0])) * 2.0 ** float(rng.uniform(-27, -12))
         beta[j] = np.float32(float(step) * (k - 0.5 + delta) - float(g) / sigma[r])
     _check(x, gamma, beta, eps, step, bits)
+
+
+@pytest.mark.parametrize("rows,cols", [(12288, 36), (12289, 36), (24576, 33), (24577, 32), (20, 4096), (20, 4128), (17, 4131),
+                                       (16, 31), (33, 96)])
+def test_rows_per_workgroup_chunk_edges_and_table_end(rows, cols):
+    """The sizes at which the rows per workgroup change, rows that end on, before and after a 32-column
+    chunk, and rows longer than the 4096-entry table of reciprocals (those steps divide)."""
+    rng = np.random.default_rng(rows + 7 * cols)
+    x, gamma, beta = _case(rng, rows, cols)
+    _check(x, gamma, beta, 1e-6, np.float32(0.4), 4)
+
+
+@pytest.mark.parametrize("cols", [64, 66])
+def test_sum_in_place_and_sum_without_residual(cols):
+    """sum_out may be x itself (the stream updated in place); without a residual it receives x."""
+    rng = np.random.default_rng(cols)
+    x, gamma, beta = _case(rng, 50, cols)
+    beta[:8] = np.float32(0.4) * np.float32(0.5)          # elements on and near boundaries: the comparator path
+    x[:, :8] = x[:, :1]
+    res = rng.standard_normal((50, cols)).astype(np.float32)
+    for r in (res, None):
+        ref = vqo.layernorm_quantize(x, gamma, beta, 1e-6, np.float32(0.4), 4, res=r, want_sum=True)
+        xd = dev(x)
+        out = vitq.QMat.empty(50, cols, 4)
+        vitq.vq_layernorm_quantize(xd, dev(r), xd, dev(gamma), dev(beta), 1e-6, 0.4, out)
+        torch.cuda.synchronize()
+        assert np.array_equal(from_qmat(out), ref["q"])
+        assert np.array_equal(xd.cpu().numpy(), ref["sum"] if r is not None else x)
