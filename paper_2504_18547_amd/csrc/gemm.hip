@@ -1116,6 +1116,176 @@ void gemm_kernel(GemmParams p) {
     }
 }
 
+// ---- few tokens: the contraction split over the waves of a workgroup ---------------------------
+// One image through a 768-wide linear is 6 to 18 tiles of the kernel above: a handful of the 256 CUs
+// walk all of K in turn, each stage a round trip to L2 that nothing hides.  What bounds such a call is
+// that chain, so here a workgroup owns one 32x32 block and its waves share K, 64 values per step, each
+// loading its operand pieces straight from L2 into registers (no LDS stage, no barrier in the loop;
+// kSplitUnroll steps requested ahead).  The int32 partial sums meet in LDS -- integer addition, so the
+// split changes no result -- and wave 0 runs the epilogue on the sum.
+constexpr int kSplitUnroll = 4;
+constexpr int kSplitMaxWaves = 8;
+
+template <int WB, int AB, int EPI>
+__global__ __launch_bounds__(kSplitMaxWaves * 64)
+void gemm_split_kernel(GemmParams p) {
+    static_assert(EPI == kEpiGeneric || EPI == kEpiF32 || EPI == kEpiQuant || EPI == kEpiQuantGelu, "epilogues");
+    constexpr bool SWAP = (EPI == kEpiF32);
+    constexpr int WBY = 32 * WB / 8, XBY = 32 * AB / 8;       // bytes of a lane's 32 values of a step
+    constexpr int WDW = WBY / 4, XDW = XBY / 4;
+    __shared__ int4 s_part[kSplitMaxWaves - 1][4][64];
+    __shared__ __attribute__((aligned(16))) float s_scs[32], s_bs[32];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6;
+    const int li = lane & 31, g = lane >> 5;
+    const int n_ct = (p.Nout + 31) / 32;
+    const int ct = blockIdx.x % n_ct;
+    const int c0 = ct * 32, t0 = (blockIdx.x / n_ct) * 32;
+
+    // wave 0 requests what its epilogue needs ahead of the operands
+    float sc = 1.0f, bs = 0.0f;
+    float rv[16];
+    const int m0 = t0 + 4 * g;                                // first token of this lane in the fp32 epilogue
+    const bool full = t0 + 32 <= p.M && c0 + 32 <= p.Nout;
+    if constexpr (EPI != kEpiGeneric) {
+        if (wave == 0) {
+            const int ch = c0 + li;
+            if (ch < p.Nout) {
+                sc = p.s_x * p.s_w[p.s_w_per_channel ? ch : 0];
+                if (p.bias) bs = p.bias[ch];
+            }
+            if constexpr (EPI == kEpiF32) {
+                if (p.res) {
+                    if (full) load_residual<true>(p, m0, c0 + li, rv);
+                    else load_residual<false>(p, m0, c0 + li, rv);
+                }
+            }
+        }
+    }
+
+    // this lane's operand rows (rows beyond the matrix are clamped: their products are never stored)
+    const uint8_t *wrow = p.w + (int64_t)min(c0 + (SWAP ? li : channel_of_slot(li)), p.Nout - 1) * p.w_stride;
+    const uint8_t *xrow = p.x + (int64_t)min(t0 + li, p.M - 1) * p.x_stride;
+    const int steps = (p.K + 63) / 64;
+    v16i acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0;
+    for (int j0 = wave; j0 < steps; j0 += waves * kSplitUnroll) {
+        u32 wr[kSplitUnroll][WDW], xr[kSplitUnroll][XDW];
+#pragma unroll
+        for (int u = 0; u < kSplitUnroll; ++u) {
+            const int j = j0 + u * waves;
+            // 16-byte pieces (8 bytes of 2-bit weights) past the end of a row, or of a step past the
+            // last one, are read from sixteen zero bytes
+#pragma unroll
+            for (int q = 0; q < (WBY + 15) / 16; ++q) {
+                const int off = j * (2 * WBY) + g * WBY + 16 * q;
+                const uint8_t *src = (off < p.kbytes_w16) ? wrow + off : reinterpret_cast<const uint8_t *>(g_zero16);
+                if constexpr (WB == 2) {
+                    const uint2 v = *reinterpret_cast<const uint2 *>(src);
+                    wr[u][0] = v.x; wr[u][1] = v.y;
+                } else {
+                    const uint4 v = *reinterpret_cast<const uint4 *>(src);
+                    wr[u][4 * q] = v.x; wr[u][4 * q + 1] = v.y; wr[u][4 * q + 2] = v.z; wr[u][4 * q + 3] = v.w;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < XBY / 16; ++q) {
+                const int off = j * (2 * XBY) + g * XBY + 16 * q;
+                const uint8_t *src = (off < p.kbytes_x16) ? xrow + off : reinterpret_cast<const uint8_t *>(g_zero16);
+                const uint4 v = *reinterpret_cast<const uint4 *>(src);
+                xr[u][4 * q] = v.x; xr[u][4 * q + 1] = v.y; xr[u][4 * q + 2] = v.z; xr[u][4 * q + 3] = v.w;
+            }
+        }
+        static_for<kSplitUnroll>([&](auto U) {
+            constexpr int u = decltype(U)::value;
+            static_for<2>([&](auto S_) {
+                constexpr int s = decltype(S_)::value;
+                v4i wf, xf;
+                if constexpr (WB == 4) wf = unpack4_x16(wr[u][2 * s], wr[u][2 * s + 1]);
+                else if constexpr (WB == 2) wf = unpack2_x64(wr[u][s]);
+                else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) wf[i] = (int)wr[u][4 * s + i];
+                }
+                if constexpr (AB == 4) {
+                    if constexpr (WB == 2) xf = unpack4_x16_order2(xr[u][2 * s], xr[u][2 * s + 1]);
+                    else xf = unpack4_x16(xr[u][2 * s], xr[u][2 * s + 1]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) xf[i] = (int)xr[u][4 * s + i];
+                }
+                if constexpr (SWAP) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(xf, wf, acc, 0, 0, 0);
+                else acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf, xf, acc, 0, 0, 0);
+            });
+        });
+    }
+
+    if (wave > 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            s_part[wave - 1][q][lane] = make_int4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+    }
+    constexpr int shift = Shift<WB, AB>::value;
+    const float folded = ldexpf(sc, -shift);
+    const bool fold_ok = __builtin_amdgcn_ballot_w64(!(ldexpf(folded, shift) == sc)) == 0;
+    if (EPI != kEpiGeneric && wave == 0 && g == 0) { s_scs[li] = folded; s_bs[li] = bs; }
+    __syncthreads();
+    if (wave > 0) return;
+    for (int w = 0; w < waves - 1; ++w) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int4 v = s_part[w][q][lane];
+            acc[4 * q] += v.x; acc[4 * q + 1] += v.y; acc[4 * q + 2] += v.z; acc[4 * q + 3] += v.w;
+        }
+    }
+
+    if constexpr (EPI == kEpiF32) {
+        const float scale = fold_ok ? folded : sc;
+        const int sh = fold_ok ? 0 : shift;
+        if (p.res) {
+            if (full) epilogue_f32<true, true>(p, acc, sh, m0, c0 + li, scale, bs, rv);
+            else epilogue_f32<false, true>(p, acc, sh, m0, c0 + li, scale, bs, rv);
+        } else {
+            if (full) epilogue_f32<true, false>(p, acc, sh, m0, c0 + li, scale, bs, rv);
+            else epilogue_f32<false, false>(p, acc, sh, m0, c0 + li, scale, bs, rv);
+        }
+    } else {
+        // the lane's sixteen channels (32 four- or eight-bit channels are whole 16-byte units, so the
+        // blocks also cover every padding byte of a packed row)
+        const int cb = c0 + 16 * g, m = t0 + li;
+        if constexpr (EPI == kEpiGeneric) {
+            epilogue_generic(p, acc, shift, m, cb);
+        } else {
+            int which;
+            uint8_t *dst = packed_dst(p, m, cb, which);
+            const float sy0 = p.s_y[0], sy1 = p.s_y[1], sy2 = p.s_y[2];
+            const float ry0 = p.r_y[0], ry1 = p.r_y[1], ry2 = p.r_y[2];
+            const float s_y = which == 0 ? sy0 : (which == 1 ? sy1 : sy2);
+            const float r_y = which == 0 ? ry0 : (which == 1 ? ry1 : ry2);
+            if (cb >= p.Nout) store_zero_group(p, dst);
+            else epilogue_quant<EPI == kEpiQuantGelu>(p, acc, shift, dst, s_y, r_y, cb, s_scs + 16 * g, s_bs + 16 * g, !fold_ok);
+        }
+    }
+}
+
+template <int WB, int AB>
+hipError_t launch_split(const GemmParams &p, int epi, hipStream_t stream) {
+    const int64_t blocks = (int64_t)((p.Nout + 31) / 32) * ((p.M + 31) / 32);
+    const int steps = (p.K + 63) / 64;
+    const int waves = steps >= 24 ? 8 : (steps >= 4 ? 4 : steps);
+    const dim3 grid((unsigned)blocks), block((unsigned)waves * 64);
+    switch (epi) {
+        case kEpiF32: hipLaunchKernelGGL((gemm_split_kernel<WB, AB, kEpiF32>), grid, block, 0, stream, p); break;
+        case kEpiQuant: hipLaunchKernelGGL((gemm_split_kernel<WB, AB, kEpiQuant>), grid, block, 0, stream, p); break;
+        case kEpiQuantGelu: hipLaunchKernelGGL((gemm_split_kernel<WB, AB, kEpiQuantGelu>), grid, block, 0, stream, p); break;
+        default: hipLaunchKernelGGL((gemm_split_kernel<WB, AB, kEpiGeneric>), grid, block, 0, stream, p); break;
+    }
+    return hipGetLastError();
+}
+
 template <int WB, int AB, int TC, int TT, int WAVES_C, int WAVES_T, int BK, int S, int OCC, int EPI>
 hipError_t launch(const GemmParams &p, hipStream_t stream) {
     constexpr size_t lds = S * ((size_t)TC * (BK * WB / 8) + (size_t)TT * (BK * AB / 8)) + 2 * TC * sizeof(float) + 16 +
@@ -1151,6 +1321,22 @@ hipError_t launch_epi(const GemmParams &p, int epi, hipStream_t stream) {
         case kEpiAbsorbedBig: return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiAbsorbedBig>(p, stream);
         default: return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiGeneric>(p, stream);
     }
+}
+
+// Does the call go to the split-contraction kernel?  It re-reads each operand row once per 32x32 block
+// (from L2), so its time grows with the number of blocks, while the tiled kernels' stays at one walk of
+// K until their tiles fill the chip.  us per call, split / tiled (4-bit 128x128 tiles, 8-bit tiles):
+//   4 bits  K  768, 504 blocks   5.0 /  10.0    8 bits  K  768, 504 blocks   6.8 / 10.6
+//   4 bits  K 3072, 168 blocks   6.0 /  22.9    8 bits  K 3072, 168 blocks   8.9 / 35.8
+//   4 bits  K  768, 936 blocks   6.6 /  10.2    8 bits  K  768, 936 blocks   9.9 / 10.8
+//   4 bits  K 4096, 800 blocks  18.5 /  23.0    8 bits  K 4096, 416 blocks  17.9 / 45.9
+//   4 bits  K 3072, 1200 blocks 23.0 /  17.7    8 bits  K  768, 1800 blocks 16.1 / 11.0
+bool use_split(const GemmParams &p, int wb, int ab, int epi) {
+    if (!((wb == 4 && ab == 4) || (wb == 2 && ab == 4) || (wb == 8 && ab == 8))) return false;
+    if (epi != kEpiGeneric && epi != kEpiF32 && epi != kEpiQuant && epi != kEpiQuantGelu) return false;
+    if (p.yq && p.yq_sb == 2) return false;              // (a 2-bit row's padding can reach past a 32-channel block)
+    const int64_t blocks = (int64_t)((p.Nout + 31) / 32) * (((int64_t)p.M + 31) / 32);
+    return blocks <= (ab == 8 ? 700 : 1000);
 }
 
 }  // namespace
@@ -1195,6 +1381,11 @@ hipError_t gemm_launch(GemmParams p, int wb, int ab, hipStream_t stream) {
                 if (epi == kEpiHeadNorm) return hipErrorInvalidValue;
                 epi = (epi == kEpiF32) ? epi : kEpiGeneric;
             }
+    }
+    if (use_split(p, wb, ab, epi)) {
+        if (wb == 4) return launch_split<4, 4>(p, epi, stream);
+        if (wb == 2) return launch_split<2, 4>(p, epi, stream);
+        return launch_split<8, 8>(p, epi, stream);
     }
     if (wb == 4 && ab == 4) return launch_epi<4, 4, VITQ_TC, VITQ_TT, VITQ_WC, VITQ_WT, VITQ_BK44, VITQ_S44, VITQ_OCC44>(p, epi, stream);
     if (wb == 2 && ab == 4) return launch_epi<2, 4, 128, 128, 2, 2, 128, 2, 4>(p, epi, stream);

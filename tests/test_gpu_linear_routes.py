@@ -1,0 +1,65 @@
+"""GPU parity of vq_linear on both sides of every rule that picks a kernel: the split-contraction
+kernel up to its limit of 32x32 blocks and just past it, the two 4-bit tile shapes, the two 8-bit
+tile shapes of a long contraction; each with accumulators + fp32, fp32 alone, packed and GELU +
+packed outputs.  Every result is the oracle's, bit for bit (integer sums, fixed fp32 sequences)."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from oracle import vqo
+from paper_2504_18547_amd import vitq
+from tests.gpu_util import dev, storage_of, to_qmat
+
+CASES = [
+    # bits_x, bits_w, M, K, Nout
+    (4, 4, 1, 1, 16), (8, 8, 33, 65, 48), (4, 2, 31, 129, 16),            # one wave, two waves, three
+    (4, 4, 5, 1535, 1001), (4, 2, 40, 1601, 80), (8, 8, 63, 1553, 37),    # eight waves, a ragged tail, odd widths
+    (4, 4, 800, 200, 1280), (4, 4, 801, 200, 1280), (4, 2, 801, 200, 1280),   # 1000 blocks of 32x32, 1040
+    (8, 8, 800, 200, 896), (8, 8, 801, 200, 896),                         # 700, 728
+    (4, 4, 12797, 40, 1024), (4, 4, 8445, 40, 1024),                      # 128x256 tiles (an even deal), 128x128
+    (8, 8, 35, 2049, 32912), (8, 8, 35, 2049, 32768),                     # 258 large tiles, 256
+]
+
+
+@pytest.mark.parametrize("bits_x,bits_w,M,K,Nout", CASES)
+def test_linear_route(bits_x, bits_w, M, K, Nout):
+    rng = np.random.default_rng(M + 3 * K + 7 * Nout + bits_w)
+    lo_x, hi_x = vqo.qrange(bits_x)
+    lo_w, hi_w = vqo.qrange(bits_w)
+    xq = rng.integers(lo_x, hi_x + 1, (M, K)).astype(np.int8)
+    wq = rng.integers(lo_w, hi_w + 1, (Nout, K)).astype(np.int8)
+    s_w = np.exp(rng.uniform(-7, -4, Nout)).astype(np.float32)
+    bias = (rng.standard_normal(Nout) * 0.01).astype(np.float32)
+    s_x, s_y = np.float32(0.31), np.float32(0.05)
+    xd, wd, swd, bd = to_qmat(xq, bits_x), to_qmat(wq, bits_w), dev(s_w), dev(bias)
+
+    def run(act, acc, y, yq):
+        vitq.vq_linear(xd, s_x, wd, swd, 1, bd, act, acc, y, s_y, yq)
+        torch.cuda.synchronize()
+
+    def packed():
+        yq = vitq.QMat.empty(M, Nout, bits_x)
+        yq.data.fill_(0xFF)                  # padding bytes of a packed row are written too
+        return yq
+
+    ref = vqo.linear(xq, s_x, wq, s_w, bias=bias, s_y=s_y, bits_y=bits_x)
+    want_q = vqo.pack(ref["yq"], storage_of(bits_x))
+    acc = torch.full((M, Nout), -7, dtype=torch.int32, device="cuda")
+    y = torch.full((M, Nout), -7.0, device="cuda")
+    yq = packed()
+    run(0, acc, y, yq)
+    assert np.array_equal(acc.cpu().numpy(), ref["acc"])
+    assert np.array_equal(y.cpu().numpy(), ref["y"])
+    assert np.array_equal(yq.data.cpu().numpy(), want_q)
+    y.fill_(-7.0)
+    run(0, None, y, None)
+    assert np.array_equal(y.cpu().numpy(), ref["y"])
+    yq = packed()
+    run(0, None, None, yq)
+    assert np.array_equal(yq.data.cpu().numpy(), want_q)
+    yq = packed()
+    run(1, None, None, yq)
+    ref = vqo.linear(xq, s_x, wq, s_w, bias=bias, act=1, s_y=s_y, bits_y=bits_x)
+    assert np.array_equal(yq.data.cpu().numpy(), vqo.pack(ref["yq"], storage_of(bits_x)))
