@@ -1339,6 +1339,21 @@ bool use_split(const GemmParams &p, int wb, int ab, int epi) {
     return blocks <= (ab == 8 ? 700 : 1000);
 }
 
+// 4-bit pairs: 128x128 tiles (four waves, two k-stages, four workgroups per CU) or 128x256 (eight
+// waves, three stages, two per CU)?  The time follows the busiest CU, so the smaller tile wins where it
+// deals the rows out more evenly (12,608 x 3072 -> 768: 300 large tiles leave two on some CUs and one on
+// most, 41.2 us; 594 small ones 35.0 us), where the tiles do not even fill the chip twice (6,304 rows of
+// the same: 26.3 -> 24.3 us) and with the GELU epilogue, whose arithmetic overlaps better with more
+// independent workgroups (50,432 x 768 -> 3072: 169.7 -> 164.8 us).  On an even deal the larger one
+// reads less (50,432 x 768 -> 2304: 103.3 us against 106.0; 18,912 x 768 -> 768: 19.4 against 20.6).
+bool small_tile(const GemmParams &p, int epi) {
+    constexpr int64_t kCUs = 256;
+    const int64_t n_ct = (p.Nout + 127) / 128;
+    const int64_t small = n_ct * (((int64_t)p.M + 127) / 128), large = n_ct * (((int64_t)p.M + 255) / 256);
+    const int64_t cs = (small + kCUs - 1) / kCUs, cl = 2 * ((large + kCUs - 1) / kCUs);   // 128x128 units of the busiest CU
+    return epi == kEpiQuantGelu || cs < cl || cs <= 2;
+}
+
 }  // namespace
 
 hipError_t gemm_launch(GemmParams p, int wb, int ab, hipStream_t stream) {
@@ -1387,14 +1402,21 @@ hipError_t gemm_launch(GemmParams p, int wb, int ab, hipStream_t stream) {
         if (wb == 2) return launch_split<2, 4>(p, epi, stream);
         return launch_split<8, 8>(p, epi, stream);
     }
-    if (wb == 4 && ab == 4) return launch_epi<4, 4, VITQ_TC, VITQ_TT, VITQ_WC, VITQ_WT, VITQ_BK44, VITQ_S44, VITQ_OCC44>(p, epi, stream);
+    if (wb == 4 && ab == 4) {
+        if (small_tile(p, epi)) return launch_epi<4, 4, 128, 128, 2, 2, VITQ_BK44, 2, 4>(p, epi, stream);
+        return launch_epi<4, 4, VITQ_TC, VITQ_TT, VITQ_WC, VITQ_WT, VITQ_BK44, VITQ_S44, VITQ_OCC44>(p, epi, stream);
+    }
     if (wb == 2 && ab == 4) return launch_epi<2, 4, 128, 128, 2, 2, 128, 2, 4>(p, epi, stream);
     if (wb == 8 && ab == 8) {
         // 8-bit operands are read from LDS at twice the bytes per product and need no unpacking: a long
         // contraction is bound by those reads and gains from 64x128 wave tiles (a quarter fewer fragment
         // reads per product, at two waves per SIMD); a short one is dominated by its epilogue, which wants
-        // four waves per SIMD.
-        if (p.K >= 2048 && (epi == kEpiF32 || epi == kEpiQuant || epi == kEpiQuantGelu))
+        // four waves per SIMD.  With no more large tiles than CUs it is the walk of K by one workgroup that
+        // takes the time, and halving the tile halves it (5,193 x 4096 -> 1024: 168 large tiles, 47.0 ->
+        // 38.5 us; 16,384 x 2048 -> 512: 256, 30.1 -> 27.9); beyond that the larger one is ahead
+        // (9,900 x 4096 -> 1024: 312, 59.2 us against 65.2; 25,216 x 2048 -> 512: 396, 38.3 against 49.0).
+        const int64_t large = (int64_t)((p.Nout + 127) / 128) * (((int64_t)p.M + 255) / 256);
+        if (p.K >= 2048 && large > 256 && (epi == kEpiF32 || epi == kEpiQuant || epi == kEpiQuantGelu))
             return launch_epi<8, 8, 128, 256, 2, 2, 64, 3, 2>(p, epi, stream);
         return launch_epi<8, 8, 128, 128, 2, 2, VITQ_BK88, VITQ_S88, VITQ_OCC88>(p, epi, stream);
     }
