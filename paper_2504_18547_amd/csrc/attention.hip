@@ -599,9 +599,12 @@ hipError_t launch_mode(const AttnParams &p, AttnMode mode, hipStream_t stream) {
 // only a handful of registers hold scores at any time, and the key count is a run-time value.
 constexpr int kStreamThreads = 1024;    // 16 waves share one head's K / V^T in LDS
 
-// (eight waves per SIMD, i.e. at most 64 registers: two workgroups share a CU when their LDS fits)
-template <int SB, bool P8, bool LUT>
-__global__ __launch_bounds__(kStreamThreads, 8) void attention_stream_kernel(AttnParams p) {
+// KEEP == 0: eight waves per SIMD, i.e. at most 64 registers, so that two workgroups share a CU.
+// KEEP > 0: one workgroup's LDS fills a CU, four waves per SIMD have 128 registers, and the exponentials
+// of the first KEEP tiles (all of real keys) stay in registers from pass B to pass C.
+template <int SB, bool P8, bool LUT, int KEEP>
+__global__ __launch_bounds__(kStreamThreads, (KEEP > 0 ? 4 : 8)) void attention_stream_kernel(AttnParams p) {
+    static_assert(KEEP % 4 == 0, "whole 64-key chunks are kept");
     constexpr int NTHR = kStreamThreads, NW = NTHR / 64;
     constexpr int KROW = 64 * SB / 8;
     using KR = KRows<SB, false>;
@@ -752,8 +755,17 @@ __global__ __launch_bounds__(kStreamThreads, 8) void attention_stream_kernel(Att
 
         // ---- pass B: integer row sum of the exponentials ---------------------------------------
         u32 sum = 0;
+        [[maybe_unused]] u32 keep[KEEP > 0 ? KEEP : 1][4];
+        static_for<KEEP>([&](auto T) {
+            constexpr int t = decltype(T)::value;
+            if constexpr (t % 4 == 0 && t > 0) __builtin_amdgcn_sched_barrier(0);      // (bounds the registers)
+            const v4i s = score_tile(t);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) keep[t][r] = exp_of(s[r]);
+            sum += (keep[t][0] + keep[t][1]) + (keep[t][2] + keep[t][3]);
+        });
 #pragma unroll 4
-        for (int t = 0; t < nt; ++t) {
+        for (int t = KEEP; t < nt; ++t) {
             u32 e[4];
             exp_tile(t, e);
             sum += (e[0] + e[1]) + (e[2] + e[3]);
@@ -766,16 +778,22 @@ __global__ __launch_bounds__(kStreamThreads, 8) void attention_stream_kernel(Att
         v4i o[4], cs[4];
 #pragma unroll
         for (int T = 0; T < 4; ++T) { o[T] = v4i{0, 0, 0, 0}; cs[T] = v4i{0, 0, 0, 0}; }
-        for (int c = 0; c < nch; ++c) {
+        auto chunk = [&](auto C, int c) {                // C >= 0: chunk number known, its exponentials kept
+            constexpr bool KEPT = decltype(C)::value >= 0;
             u32 pp[4];
             float worst = 0.0f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int t = 4 * c + j;
                 u32 packed = 0;
-                if (t < nt) {
+                if (KEPT || t < nt) {
                     u32 e[4];
-                    exp_tile(t, e);
+                    if constexpr (KEPT) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) e[r] = keep[4 * decltype(C)::value + j][r];
+                    } else {
+                        exp_tile(t, e);
+                    }
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const float x = (float)e[r] * inv;
@@ -822,7 +840,9 @@ __global__ __launch_bounds__(kStreamThreads, 8) void attention_stream_kernel(Att
                     cs[T] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf, ones, cs[T], 0, 0, 0);
                 }
             }
-        }
+        };
+        static_for<KEEP / 4>([&](auto C) { chunk(C, decltype(C)::value); });
+        for (int c = KEEP / 4; c < nch; ++c) chunk(std::integral_constant<int, -1>{}, c);
 
         // ---- output: scale, requantize (guarded), pack ------------------------------------------
         if (qok) {
@@ -880,13 +900,9 @@ __global__ __launch_bounds__(kStreamThreads, 8) void attention_stream_kernel(Att
     }
 }
 
-template <int SB, bool P8, bool LUT>
-hipError_t launch_stream(const AttnParams &p, hipStream_t stream) {
-    constexpr int KPITCH = KRows<SB, false>::pitch;
-    const int nch = ((p.N + 15) / 16 + 3) / 4;
-    const size_t lds = (((size_t)nch * 64 * KPITCH + 15) & ~(size_t)15) + (size_t)64 * (nch * 64 + 16) +
-                       (LUT ? (size_t)p.lut_n * 4 : 0);
-    auto kern = attention_stream_kernel<SB, P8, LUT>;
+template <int SB, bool P8, bool LUT, int KEEP>
+hipError_t launch_stream_keep(const AttnParams &p, size_t lds, hipStream_t stream) {
+    auto kern = attention_stream_kernel<SB, P8, LUT, KEEP>;
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -895,6 +911,23 @@ hipError_t launch_stream(const AttnParams &p, hipStream_t stream) {
     dim3 grid((unsigned)(p.B * p.H), (unsigned)p.qsplit);
     hipLaunchKernelGGL(kern, grid, dim3(kStreamThreads), lds, stream, p);
     return hipGetLastError();
+}
+
+template <int SB, bool P8, bool LUT>
+hipError_t launch_stream(const AttnParams &p, hipStream_t stream) {
+    constexpr int KPITCH = KRows<SB, false>::pitch;
+    [[maybe_unused]] constexpr int KEEP = 16;            // (64 of the 128 registers)
+    const int nch = ((p.N + 15) / 16 + 3) / 4;
+    const size_t lds = (((size_t)nch * 64 * KPITCH + 15) & ~(size_t)15) + (size_t)64 * (nch * 64 + 16) +
+                       (LUT ? (size_t)p.lut_n * 4 : 0);
+    // Past half a CU's 160 KB a second workgroup would not fit, so the registers it would need are free for
+    // the exponentials (8-bit operands from 513 keys; 4-bit ones stay below and keep the occupancy, with
+    // which they measured the same).  Attention block, 8 bits, 577 keys: 9 images x 16 heads 144.7 -> 134.5 us,
+    // 64 x 12 496 -> 452; the 64-register form also spilled.
+    if constexpr (SB == 8) {
+        if (lds > 80 * 1024 && p.N >= 16 * KEEP) return launch_stream_keep<SB, P8, LUT, KEEP>(p, lds, stream);
+    }
+    return launch_stream_keep<SB, P8, LUT, 0>(p, lds, stream);
 }
 
 template <int SB>
