@@ -375,9 +375,8 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
     [[maybe_unused]] auto d8 = [&](float t) { return rintf(t) - qminf; };      // (rounded first: adding the bias would round again)
     // packs the four levels (one byte each, biased by -qmin) of columns c0.. of a row and stores them
     uint8_t *const out0 = p.out + row0 * p.out_stride;
-    const u32 ostride = (u32)p.out_stride;
-    auto store_levels = [&](int r, int c0, u32 w) {
-        uint8_t *dst = out0 + (u32)r * (uint64_t)ostride + (u32)(c0 * SB / 8);
+    auto store_levels = [&](int r, int c0, u32 w) {       // (r is uniform: the 64-bit product is scalar)
+        uint8_t *dst = out0 + r * p.out_stride + (u32)(c0 * SB / 8);
         if constexpr (SB == 8) w = ((w & 0x7F7F7F7Fu) + (unbias & 0x7F7F7F7Fu)) ^ ((w ^ unbias) & 0x80808080u);
         else w = (w + unbias) & (((1u << SB) - 1u) * 0x01010101u);
         if (padded != cols) {                             // zeros beyond the last column

@@ -194,3 +194,18 @@ def test_sum_in_place_and_sum_without_residual(cols):
         torch.cuda.synchronize()
         assert np.array_equal(from_qmat(out), ref["q"])
         assert np.array_equal(xd.cpu().numpy(), ref["sum"] if r is not None else x)
+
+
+@pytest.mark.parametrize("stride", [1 << 32, (1 << 32) + 48])
+def test_output_rows_more_than_four_gib_apart(stride):
+    """The output stride is a 64-bit number of bytes: two rows 2^32 bytes apart and further."""
+    rng = np.random.default_rng(32)
+    x, gamma, beta = _case(rng, 2, 96)
+    out = vitq.QMat.empty(2, 96, 4, row_stride=stride)
+    out.data[:, :64].fill_(0xFF)
+    vitq.vq_layernorm_quantize(dev(x), None, None, dev(gamma), dev(beta), 1e-6, 0.4, out)
+    torch.cuda.synchronize()
+    want = vqo.pack(vqo.layernorm_quantize(x, gamma, beta, 1e-6, np.float32(0.4), 4)["q"], 4)
+    got = out.data[:, :64].cpu().numpy()
+    assert np.array_equal(got[:, :48], want[:, :48])
+    assert (got[:, 48:] == 0xFF).all()                    # nothing beyond the padded row
