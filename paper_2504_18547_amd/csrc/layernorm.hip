@@ -618,6 +618,21 @@ hipError_t layernorm_quantize_launch(const LnParams &p, hipStream_t stream) {
     // 197 rows 50 -> 19.5, 12,608 rows 59 -> 32, 25,216 rows 64 -> 40, 50,432 rows 76 -> 72, 100,000 rows 154 -> 117.
     const int64_t slots = 3 * 256;
     const int R = p.rows <= 16 * slots ? 16 : (p.rows <= 32 * slots ? 32 : 64);
+    // A grid holds at most 2^32 - 1 work-items: more rows than that (613 million) go in several launches.
+    constexpr int64_t kMaxBlocks = (int64_t)UINT32_MAX / (kLnWaves * 64);
+    if (p.rows > kMaxBlocks * R) {
+        for (int64_t row = 0; row < p.rows; row += kMaxBlocks * R) {
+            LnParams part = p;
+            part.rows = min(p.rows - row, kMaxBlocks * R);
+            part.x = p.x + row * p.ld;
+            if (p.res) part.res = p.res + row * p.ld;
+            if (p.sum_out) part.sum_out = p.sum_out + row * p.ld;
+            part.out = p.out + row * p.out_stride;
+            const hipError_t e = layernorm_quantize_launch(part, stream);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     const unsigned blocks = (unsigned)((p.rows + R - 1) / R);
     auto launch = [&](auto M, auto SB) {
         constexpr int mode = decltype(M)::value, sb = decltype(SB)::value;

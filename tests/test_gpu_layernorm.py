@@ -209,3 +209,23 @@ def test_output_rows_more_than_four_gib_apart(stride):
     got = out.data[:, :64].cpu().numpy()
     assert np.array_equal(got[:, :48], want[:, :48])
     assert (got[:, 48:] == 0xFF).all()                    # nothing beyond the padded row
+
+
+def test_more_rows_than_one_grid_holds():
+    """A grid holds at most 2^32 - 1 work-items, i.e. 613,566,720 rows in workgroups of 448 for 64 rows: a
+    longer matrix is dealt to several launches.  Rows at the start, around that edge and at the end by
+    the oracle; every row's padding shows that it was written."""
+    edge = (2 ** 32 - 1) // 448 * 64
+    rows, cols = edge + 1000, 4
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(6)
+    x = torch.randn((rows, cols), generator=gen, device="cuda")
+    rng = np.random.default_rng(6)
+    _, gamma, beta = _case(rng, 1, cols)
+    out = vitq.QMat(torch.full((rows, 16), 0xFF, dtype=torch.uint8, device="cuda"), cols, 4, 4)
+    vitq.vq_layernorm_quantize(x, None, None, dev(gamma), dev(beta), 1e-6, 0.4, out)
+    torch.cuda.synchronize()
+    for lo, hi in ((0, 100), (edge - 100, edge + 100), (rows - 100, rows)):
+        ref = vqo.layernorm_quantize(x[lo:hi].cpu().numpy(), gamma, beta, 1e-6, np.float32(0.4), 4)
+        assert np.array_equal(out.data[lo:hi].cpu().numpy(), vqo.pack(ref["q"], 4))
+    assert int(out.data[:, 2:].view(torch.int16).count_nonzero()) == 0
