@@ -229,3 +229,19 @@ def test_more_rows_than_one_grid_holds():
         ref = vqo.layernorm_quantize(x[lo:hi].cpu().numpy(), gamma, beta, 1e-6, np.float32(0.4), 4)
         assert np.array_equal(out.data[lo:hi].cpu().numpy(), vqo.pack(ref["q"], 4))
     assert int(out.data[:, 2:].view(torch.int16).count_nonzero()) == 0
+
+
+@pytest.mark.parametrize("rows,cols", [(20, 768), (12289, 64), (24577, 260)])
+@pytest.mark.parametrize("off", [1, 2, 3])
+def test_gamma_and_beta_at_any_float_address(rows, cols, off):
+    """Parameters that are slices of a flat buffer: 4, 8 and 12 bytes past a 16-byte boundary, with aligned rows."""
+    rng = np.random.default_rng(rows + off)
+    x, gamma, beta = _case(rng, rows, cols)
+    flat = torch.zeros(2 * cols + 8, device="cuda")
+    gd, bd = flat[off:off + cols], flat[off + cols + 1:off + 2 * cols + 1]
+    gd.copy_(dev(gamma))
+    bd.copy_(dev(beta))
+    out = vitq.QMat.empty(rows, cols, 4)
+    vitq.vq_layernorm_quantize(dev(x), None, None, gd, bd, 1e-6, 0.4, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(from_qmat(out), vqo.layernorm_quantize(x, gamma, beta, 1e-6, np.float32(0.4), 4)["q"])
