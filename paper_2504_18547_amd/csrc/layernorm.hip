@@ -78,9 +78,15 @@ __device__ __forceinline__ float2 ln_walk_row(const float *xr, const float *rr, 
 }
 
 // R rows per workgroup: see layernorm_quantize_launch.
+// SHORT: rows of at most kXBufs chunks (128 columns).  There the level pass is what bounds the call: three
+// round trips to memory for rows that LDS still holds, and 8 to 32 of a wave's 64 lanes at work.  So the rows
+// stay in LDS and a wave decides 64 >> gsh of them side by side.  us, one walk per lane on one wave / seven
+// waves without this / with it: 400,000 x 16 8-bit 58 / 76 / 41, 400,000 x 128 83 / 93 / 76,
+// 100,000 x 31 37 / 40 / 26, 197 x 128 13.1 / 6.2 / 5.8.  (One row of under 32 columns is where the
+// first is still ahead, by 0.3 to 1 us: nothing there hides the hand-over between the waves.)
 // A chunk in LDS: 16-byte group c (four columns) of row r at c * (R + 1) + r, so that a wave reads one group of
 // its rows contiguously, at offsets from one base that are compile-time constants.
-template <int MODE, int SB, int R>
+template <int MODE, int SB, int R, bool SHORT>
 __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(LnParams p) {
     constexpr int CH = kLnCols, NW = kLnWaves, LW = kLnLoaders;
     constexpr int kGroups = CH / 4, CQ = kGroups * (R + 1);
@@ -226,6 +232,7 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
             }
         };
         auto put = [&](int ch, const Piece &v) {
+            if (SHORT && ch >= nch) return;
             float4 *dst = s_x + (ch % kXBufs) * CQ;
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
@@ -245,7 +252,8 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
             put(1, pre[1]);
             fetch(kDepth + 1, pre[1]);
             __syncthreads();
-            // step t stores chunk t + 2, held in pre[(t + 2) % kDepth] (past the last chunk: into a free buffer)
+            // step t stores chunk t + 2, held in pre[(t + 2) % kDepth] (past the last chunk: into a free buffer,
+            // or, if the rows stay, not at all)
             int t = 0;
             for (; t + kDepth <= nch + 1; t += kDepth)
                 static_for<kDepth>([&](auto D) {
@@ -270,12 +278,18 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
     // exchanged. ----
     constexpr int ROWS = (R + NW - 1) / NW;               // rows of a wave
     constexpr int HALVES = (ROWS + 3) / 4;                // (many rows: a part of them per pass)
-    constexpr int NB = (ROWS + HALVES - 1) / HALVES;      // of them per pass
-    constexpr int BL = NB <= 3 ? 2 : 1;
+    constexpr int NB = SHORT ? 2 : (ROWS + HALVES - 1) / HALVES;      // of them per pass
+    constexpr int BL = NB <= 3 && !SHORT ? 2 : 1;
     const int nrows = (int)min((int64_t)R, p.rows - row0);
     const int padded = p.row_bytes16 * 8 / SB;            // columns of the 16-byte padded row
+    // (SHORT: a row takes 1 << gsh lanes)
+    const int gsh = !SHORT ? 6 : padded <= 16 ? 2 : padded <= 32 ? 3 : padded <= 64 ? 4 : 5;
+    const int gl = lane & ((1 << gsh) - 1);               // this lane's group of four columns
     float4 xv[BL][NB], gv[BL], bv[BL];
-    auto row_of = [&](int pass, int k) { return wave + NW * (k + NB * (pass % HALVES)); };
+    auto row_of = [&](int pass, int k) {
+        if constexpr (SHORT) return ((wave + NW * (k + NB * pass)) << (6 - gsh)) + (lane >> gsh);
+        else return wave + NW * (k + NB * (pass % HALVES));
+    };
     auto element = [&](int64_t at, int c) {
         float t = p.x[at + c];
         if (p.res) t = t + p.res[at + c];
@@ -289,10 +303,21 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
         const v4f_any v = *reinterpret_cast<const v4f_any *>(reinterpret_cast<const char *>(base) + off);
         return make_float4(v.x, v.y, v.z, v.w);
     };
+    auto load_params = [&](int c0, int bl) {
+        if constexpr (VEC) {
+            gv[bl] = load4(p.gamma, 4u * (u32)min(c0, cols - 4));
+            bv[bl] = load4(p.beta, 4u * (u32)min(c0, cols - 4));
+        } else {
+            const int c[4] = {min(c0, cols - 1), min(c0 + 1, cols - 1), min(c0 + 2, cols - 1), min(c0 + 3, cols - 1)};
+            gv[bl] = make_float4(p.gamma[c[0]], p.gamma[c[1]], p.gamma[c[2]], p.gamma[c[3]]);
+            bv[bl] = make_float4(p.beta[c[0]], p.beta[c[1]], p.beta[c[2]], p.beta[c[3]]);
+        }
+    };
     auto load_pass = [&](int pass) {                      // (columns and rows beyond the matrix: clamped, not used)
         int64_t at[NB];
         int r = min(row_of(pass, 0), nrows - 1);
         at[0] = (row0 + r) * p.ld;
+        [[maybe_unused]] const int grp = min(gl, nch * kGroups - 1);
 #pragma unroll
         for (int k = 1; k < NB; ++k) {
             const bool more = r + NW < nrows;
@@ -301,12 +326,14 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
         }
 #pragma unroll
         for (int bl = 0; bl < BL; ++bl) {
-            const int c0 = 4 * lane + 256 * (pass / HALVES * BL + bl);
+            const int c0 = 4 * gl + (SHORT ? 0 : 256 * (pass / HALVES * BL + bl));
             [[maybe_unused]] const int c[4] = {min(c0, cols - 1), min(c0 + 1, cols - 1), min(c0 + 2, cols - 1), min(c0 + 3, cols - 1)};
 #pragma unroll
             for (int k = 0; k < NB; ++k) {
                 float4 &v = xv[bl][k];
-                if constexpr (VEC) {
+                if constexpr (SHORT) {
+                    v = s_x[(grp / kGroups) * CQ + (grp % kGroups) * (R + 1) + min(row_of(pass, k), nrows - 1)];
+                } else if constexpr (VEC) {
                     const u32 cv = 4u * (u32)min(c0, cols - 4);
                     v = load4(p.x + at[k], cv);
                     if constexpr (MODE == kLnRes) {
@@ -319,20 +346,14 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
                     v = make_float4(element(at[k], c[0]), element(at[k], c[1]), element(at[k], c[2]), element(at[k], c[3]));
                 }
             }
-            if constexpr (VEC) {
-                gv[bl] = load4(p.gamma, 4u * (u32)min(c0, cols - 4));
-                bv[bl] = load4(p.beta, 4u * (u32)min(c0, cols - 4));
-            } else {
-                gv[bl] = make_float4(p.gamma[c[0]], p.gamma[c[1]], p.gamma[c[2]], p.gamma[c[3]]);
-                bv[bl] = make_float4(p.beta[c[0]], p.beta[c[1]], p.beta[c[2]], p.beta[c[3]]);
-            }
+            load_params(c0, bl);
         }
     };
     load_pass(0);
 
-    // the chunks are done with: their LDS holds the statistics from here on
-    float4 *s_row = s_ln;                                 // [R] mean, guess of 1/(sigma*step), 0 (or infinity: no guess), V
-    float *s_m2 = reinterpret_cast<float *>(s_ln + R);    // [R] sum of squared deviations
+    // the running means are done with: their LDS holds the statistics from here on
+    float4 *s_row = s_m;                                  // [R] mean, guess of 1/(sigma*step), 0 (or infinity: no guess), V
+    float *s_m2 = reinterpret_cast<float *>(s_m + R);     // [R] sum of squared deviations
     u32 *s_least = reinterpret_cast<u32 *>(s_m2 + R);
     if (lane < R) {
         if (role == 1) s_m2[lane] = m2;
@@ -379,7 +400,7 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
     [[maybe_unused]] auto d8 = [&](float t) { return rintf(t) - qminf; };      // (rounded first: adding the bias would round again)
     // packs the four levels (one byte each, biased by -qmin) of columns c0.. of a row and stores them
     uint8_t *const out0 = p.out + row0 * p.out_stride;
-    auto store_levels = [&](int r, int c0, u32 w) {       // (r is uniform: the 64-bit product is scalar)
+    auto store_levels = [&](int r, int c0, u32 w) {       // (without SHORT r is uniform, the 64-bit product scalar)
         uint8_t *dst = out0 + r * p.out_stride + (u32)(c0 * SB / 8);
         if constexpr (SB == 8) w = ((w & 0x7F7F7F7Fu) + (unbias & 0x7F7F7F7Fu)) ^ ((w ^ unbias) & 0x80808080u);
         else w = (w + unbias) & (((1u << SB) - 1u) * 0x01010101u);
@@ -392,12 +413,12 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
             *reinterpret_cast<uint16_t *>(dst) = (uint16_t)__builtin_amdgcn_perm(0u, w | (w >> 4), 0x0C0C0200u);
         else *dst = (uint8_t)(w | (w >> 6) | (w >> 12) | (w >> 18));
     };
-    for (int pass = 0; pass / HALVES * BL * 256 < padded; ++pass) {
+    for (int pass = 0; SHORT ? row_of(pass, 0) - (lane >> gsh) < nrows : pass / HALVES * BL * 256 < padded; ++pass) {
         if (pass > 0) load_pass(pass);
         u32 redo = 0;                                     // (wave-uniform) items to be decided by the comparator
         static_for<BL>([&](auto BLK) {
             constexpr int bl = decltype(BLK)::value;
-            const int c0 = 4 * lane + 256 * (pass / HALVES * BL + bl);
+            const int c0 = 4 * gl + (SHORT ? 0 : 256 * (pass / HALVES * BL + bl));
             if (c0 >= padded) return;
             const float gm[4] = {gv[bl].x, gv[bl].y, gv[bl].z, gv[bl].w}, bt[4] = {bv[bl].x, bv[bl].y, bv[bl].z, bv[bl].w};
             float btr[4], bmax = 0.0f, odd = 0.0f;
@@ -453,8 +474,8 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
         while (redo) {
             const int item = __builtin_ctz(redo);
             redo &= redo - 1;
-            const int c0 = 4 * lane + 256 * (pass / HALVES * BL + item / NB), r = row_of(pass, item % NB);
-            if (c0 >= padded) continue;
+            const int c0 = 4 * gl + (SHORT ? 0 : 256 * (pass / HALVES * BL + item / NB)), r = row_of(pass, item % NB);
+            if (c0 >= padded || r >= nrows) continue;
             const float4 st = s_row[r];
             const float V = st.w;
             const int c[4] = {c0, min(c0 + 1, cols - 1), min(c0 + 2, cols - 1), min(c0 + 3, cols - 1)};
@@ -639,9 +660,14 @@ hipError_t layernorm_quantize_launch(const LnParams &p, hipStream_t stream) {
     const unsigned blocks = (unsigned)((p.rows + R - 1) / R);
     auto launch = [&](auto M, auto SB) {
         constexpr int mode = decltype(M)::value, sb = decltype(SB)::value;
-        if (R == 16) hipLaunchKernelGGL((layernorm_quantize_kernel<mode, sb, 16>), dim3(blocks), dim3(kLnWaves * 64), 0, stream, p);
-        else if (R == 32) hipLaunchKernelGGL((layernorm_quantize_kernel<mode, sb, 32>), dim3(blocks), dim3(kLnWaves * 64), 0, stream, p);
-        else hipLaunchKernelGGL((layernorm_quantize_kernel<mode, sb, 64>), dim3(blocks), dim3(kLnWaves * 64), 0, stream, p);
+        auto launch_rows = [&](auto ROWS) {
+            constexpr int R_ = decltype(ROWS)::value;
+            if (p.cols <= kXBufs * kLnCols) hipLaunchKernelGGL((layernorm_quantize_kernel<mode, sb, R_, true>), dim3(blocks), dim3(kLnWaves * 64), 0, stream, p);
+            else hipLaunchKernelGGL((layernorm_quantize_kernel<mode, sb, R_, false>), dim3(blocks), dim3(kLnWaves * 64), 0, stream, p);
+        };
+        if (R == 16) launch_rows(std::integral_constant<int, 16>{});
+        else if (R == 32) launch_rows(std::integral_constant<int, 32>{});
+        else launch_rows(std::integral_constant<int, 64>{});
     };
     auto launch_mode = [&](auto SB) {
         if (!vec) launch(std::integral_constant<int, kLnScalar>{}, SB);

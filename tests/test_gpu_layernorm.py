@@ -245,3 +245,26 @@ def test_gamma_and_beta_at_any_float_address(rows, cols, off):
     vitq.vq_layernorm_quantize(dev(x), None, None, gd, bd, 1e-6, 0.4, out)
     torch.cuda.synchronize()
     assert np.array_equal(from_qmat(out), vqo.layernorm_quantize(x, gamma, beta, 1e-6, np.float32(0.4), 4)["q"])
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("rows", [1, 57, 12300, 24600])           # one per rows-per-workgroup, whole and cut short
+@pytest.mark.parametrize("cols", [1, 16, 33, 65, 100, 128, 129])
+def test_short_rows_side_by_side(rows, cols, bits):
+    """Rows of up to 128 columns stay in LDS and a wave decides 2 to 16 of them at once: every number of lanes
+    per row (16, 32, 64 and 128 padded columns), the first longer rows, columns on a boundary (gamma 0)
+    that go through the comparator, residual and sum in place."""
+    rng = np.random.default_rng(rows + 1000 * cols + bits)
+    x, gamma, beta = _case(rng, rows, cols)
+    step = np.float32(2.5 / vqo.qrange(bits)[1])
+    gamma[::5], beta[::5] = 0.0, step * np.float32(0.5)
+    _check(x, gamma, beta, 1e-6, step, bits)
+    res = rng.standard_normal((rows, cols)).astype(np.float32)
+    ref = vqo.layernorm_quantize(x, gamma, beta, 1e-6, step, bits, res=res, want_sum=True)
+    xd = dev(x)
+    out = vitq.QMat.empty(rows, cols, bits)
+    out.data.fill_(0xFF)
+    vitq.vq_layernorm_quantize(xd, dev(res), xd, dev(gamma), dev(beta), 1e-6, step, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.data.cpu().numpy(), vqo.pack(ref["q"], storage_of(bits)))
+    assert np.array_equal(xd.cpu().numpy(), ref["sum"])
