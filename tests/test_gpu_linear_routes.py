@@ -14,8 +14,10 @@ from tests.gpu_util import dev, storage_of, to_qmat
 
 CASES = [
     # bits_x, bits_w, M, K, Nout
-    (4, 4, 1, 1, 16), (8, 8, 33, 65, 48), (4, 2, 31, 129, 16),            # one wave, two waves, three
-    (4, 4, 5, 1535, 1001), (4, 2, 40, 1601, 80), (8, 8, 63, 1553, 37),    # eight waves, a ragged tail, odd widths
+    (4, 4, 1, 1, 16), (8, 8, 33, 65, 48), (4, 2, 31, 129, 16),            # one wave: one step, two, three
+    (4, 4, 33, 256, 48), (4, 4, 33, 257, 48), (8, 8, 20, 513, 32),        # one full wave, two waves, three
+    (4, 4, 5, 1535, 1001), (4, 2, 40, 1601, 80), (8, 8, 63, 1553, 37),    # six waves and seven, a ragged tail, odd widths
+    (4, 4, 33, 2048, 48), (4, 2, 33, 2049, 48), (8, 8, 40, 3072, 64),     # eight; two rounds of five and of six
     (4, 4, 800, 200, 1280), (4, 4, 801, 200, 1280), (4, 2, 801, 200, 1280),   # 1000 blocks of 32x32, 1040
     (8, 8, 800, 200, 896), (8, 8, 801, 200, 896),                         # 700, 728
     (4, 4, 12797, 40, 1024), (4, 4, 8445, 40, 1024),                      # 128x256 tiles (an even deal), 128x128
