@@ -1330,18 +1330,27 @@ hipError_t launch_epi(const GemmParams &p, int epi, hipStream_t stream) {
 
 // Does the call go to the split-contraction kernel?  It re-reads each operand row once per 32x32 block
 // (from L2), so its time grows with the number of blocks, while the tiled kernels' stays at one walk of
-// K until their tiles fill the chip.  us per call, split / tiled (4-bit 128x128 tiles, 8-bit tiles):
-//   4 bits  K  768, 504 blocks   5.0 /  10.0    8 bits  K  768, 504 blocks   6.8 / 10.6
-//   4 bits  K 3072, 168 blocks   6.0 /  22.9    8 bits  K 3072, 168 blocks   8.9 / 35.8
-//   4 bits  K  768, 936 blocks   6.6 /  10.2    8 bits  K  768, 936 blocks   9.9 / 10.8
-//   4 bits  K 4096, 800 blocks  18.5 /  23.0    8 bits  K 4096, 416 blocks  17.9 / 45.9
-//   4 bits  K 3072, 1200 blocks 23.0 /  17.7    8 bits  K  768, 1800 blocks 16.1 / 11.0
+// K until their tiles fill the chip.  The tiled kernel's time over the split one's, fp32 out / requantized
+// (788 to 1,576 rows; 32 rows and more channels, or 32 channels, are ahead by more in fp32, by less packed):
+//             500 blocks   800          992          1184         1500
+//   4 bits  K  384  1.45 / 1.57  1.36 / 1.47  1.44 / 1.40  1.20 / 1.32  1.07 / 0.92
+//           K 1024  1.65 / 1.65  1.20 / 1.28  1.23 / 1.22  1.00 / 1.09  0.94 / 0.91
+//           K 3072  1.90 / 1.84  1.15 / 1.20  1.14 / 1.14  0.87 / 0.91  0.84 / 0.77
+//   2 bits  K 1024  1.67 / 1.70  1.27 / 1.38  1.27 / 1.27  1.03 / 1.09  0.97 / 1.03
+//             500 blocks   600          800          992
+//   8 bits  K  384  1.26 / 1.55  1.12 / 1.39  1.00 / 1.26  1.01 / 1.20
+//           K 1024  1.44 / 1.62  1.16 / 1.31  0.97 / 1.15  0.97 / 1.10
+//           K 4096  1.65 / 1.56  1.20 / 1.16  0.94 / 0.97  0.88 / 0.89
+// Eight-bit operands too large for the caches stream from HBM, where the long row pieces of the tiled
+// kernel are read faster once every CU has two blocks: 32 x 16,384 -> 22,400 (700 blocks) 115 us tiled,
+// 171 split; 32 x 16,384 -> 16,000 (500) 1.2 times ahead as above.
 bool use_split(const GemmParams &p, int wb, int ab, int epi) {
     if (!((wb == 4 && ab == 4) || (wb == 2 && ab == 4) || (wb == 8 && ab == 8))) return false;
     if (epi != kEpiGeneric && epi != kEpiF32 && epi != kEpiQuant && epi != kEpiQuantGelu) return false;
     if (p.yq && p.yq_sb == 2) return false;              // (a 2-bit row's padding can reach past a 32-channel block)
     const int64_t blocks = (int64_t)((p.Nout + 31) / 32) * (((int64_t)p.M + 31) / 32);
-    return blocks <= (ab == 8 ? 700 : 1000);
+    const bool from_hbm = ((int64_t)p.Nout + p.M) * p.K * ab / 8 > (128 << 20);
+    return blocks <= (ab == 8 ? (from_hbm ? 512 : 700) : 1000);
 }
 
 // 4-bit pairs: 128x128 tiles (four waves, two k-stages, four workgroups per CU) or 128x256 (eight

@@ -20,6 +20,7 @@ CASES = [
     (4, 4, 33, 2048, 48), (4, 2, 33, 2049, 48), (8, 8, 40, 3072, 64),     # eight; two rounds of five and of six
     (4, 4, 800, 200, 1280), (4, 4, 801, 200, 1280), (4, 2, 801, 200, 1280),   # 1000 blocks of 32x32, 1040
     (8, 8, 800, 200, 896), (8, 8, 801, 200, 896),                         # 700, 728
+    (8, 8, 32, 8193, 16448),                                              # 514 blocks of more than 128 MB: tiled
     (4, 4, 12797, 40, 1024), (4, 4, 8445, 40, 1024),                      # 128x256 tiles (an even deal), 128x128
     (8, 8, 35, 2049, 32912), (8, 8, 35, 2049, 32768),                     # 258 large tiles, 256
 ]
