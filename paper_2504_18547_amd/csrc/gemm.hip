@@ -1356,15 +1356,22 @@ bool use_split(const GemmParams &p, int wb, int ab, int epi) {
 // 4-bit pairs: 128x128 tiles (four waves, two k-stages, four workgroups per CU) or 128x256 (eight
 // waves, three stages, two per CU)?  The time follows the busiest CU, so the smaller tile wins where it
 // deals the rows out more evenly (12,608 x 3072 -> 768: 300 large tiles leave two on some CUs and one on
-// most, 41.2 us; 594 small ones 35.0 us), where the tiles do not even fill the chip twice (6,304 rows of
-// the same: 26.3 -> 24.3 us) and with the GELU epilogue, whose arithmetic overlaps better with more
-// independent workgroups (50,432 x 768 -> 3072: 169.7 -> 164.8 us).  On an even deal the larger one
-// reads less (50,432 x 768 -> 2304: 103.3 us against 106.0; 18,912 x 768 -> 768: 19.4 against 20.6).
+// most, 40.7 us; 594 small ones 34.4), where the tiles do not even fill the chip twice (6,304 rows of
+// the same: 26.4 -> 24.8 us; 12,608 x 384 -> 384 9.3 -> 9.0) and with the GELU epilogue, whose arithmetic
+// overlaps better with more independent workgroups (50,432 x 768 -> 3072: 170 -> 161 us).  On an even deal
+// the larger one reads less (6,304 x 768 -> 2304 in fp32 18.0 us against 18.2).
+// The integer-only epilogue has less room for its references on the smaller tile (four waves stage what
+// eight do: 9 spilled registers against 5), so an even deal of any size keeps the larger one (6,304 x 768 ->
+// 768: 16.2 us against 16.9).  With more than 15 references per channel (49 spilled against 23) the deal has
+// to save a quarter: 1,576 x 768 -> 768 in 8 bits 37.0 us on large tiles, 30.8 on small ones, 12,608 rows
+// 64.1 and 61.4, but 25,216 rows 101 and 110, 6,304 rows 38.3 and 43.4, 50,432 x 768 -> 3072 601 and 724.
 bool small_tile(const GemmParams &p, int epi) {
     constexpr int64_t kCUs = 256;
     const int64_t n_ct = (p.Nout + 127) / 128;
     const int64_t small = n_ct * (((int64_t)p.M + 127) / 128), large = n_ct * (((int64_t)p.M + 255) / 256);
     const int64_t cs = (small + kCUs - 1) / kCUs, cl = 2 * ((large + kCUs - 1) / kCUs);   // 128x128 units of the busiest CU
+    if (epi == kEpiAbsorbedBig) return 4 * cs <= 3 * cl;
+    if (epi == kEpiAbsorbed) return cs < cl;
     return epi == kEpiQuantGelu || cs < cl || cs <= 2;
 }
 
