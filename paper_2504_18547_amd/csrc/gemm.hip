@@ -1360,6 +1360,9 @@ bool use_split(const GemmParams &p, int wb, int ab, int epi) {
 // the same: 26.4 -> 24.8 us; 12,608 x 384 -> 384 9.3 -> 9.0) and with the GELU epilogue, whose arithmetic
 // overlaps better with more independent workgroups (50,432 x 768 -> 3072: 170 -> 161 us).  On an even deal
 // the larger one reads less (6,304 x 768 -> 2304 in fp32 18.0 us against 18.2).
+// Large fp32 results of a long contraction are bound by their stores, and a deal that saves less than a
+// sixteenth does not make up for twice the tiles: 28,368 x 1024 -> 3072 113 us on large tiles, 121 on small
+// ones, 44,128 rows 181 and 190 (4096 channels: within 2 % either way).
 // The integer-only epilogue has less room for its references on the smaller tile (four waves stage what
 // eight do: 9 spilled registers against 5), so an even deal of any size keeps the larger one (6,304 x 768 ->
 // 768: 16.2 us against 16.9).  With more than 15 references per channel (49 spilled against 23) the deal has
@@ -1372,6 +1375,7 @@ bool small_tile(const GemmParams &p, int epi) {
     const int64_t cs = (small + kCUs - 1) / kCUs, cl = 2 * ((large + kCUs - 1) / kCUs);   // 128x128 units of the busiest CU
     if (epi == kEpiAbsorbedBig) return 4 * cs <= 3 * cl;
     if (epi == kEpiAbsorbed) return cs < cl;
+    if (epi == kEpiF32 && p.K >= 1024 && cl > 16) return false;
     return epi == kEpiQuantGelu || cs < cl || cs <= 2;
 }
 

@@ -1,7 +1,8 @@
 """GPU parity of vq_linear on both sides of every rule that picks a kernel: the split-contraction
 kernel up to its limit of 32x32 blocks and just past it, the two 4-bit tile shapes, the two 8-bit
 tile shapes of a long contraction; each with accumulators + fp32, fp32 alone, packed and GELU +
-packed outputs.  Every result is the oracle's, bit for bit (integer sums, fixed fp32 sequences)."""
+packed outputs.  Every result is the oracle's, bit for bit (integer sums, fixed fp32 sequences);
+of the larger calls it computes a sample of the rows, which are independent."""
 import numpy as np
 import pytest
 import torch
@@ -66,3 +67,53 @@ def test_linear_route(bits_x, bits_w, M, K, Nout):
     run(1, None, None, yq)
     ref = vqo.linear(xq, s_x, wq, s_w, bias=bias, act=1, s_y=s_y, bits_y=bits_x)
     assert np.array_equal(yq.data.cpu().numpy(), vqo.pack(ref["yq"], storage_of(bits_x)))
+
+
+TILED = [
+    # bits_x, bits_w, M, K, Nout: past the split kernel's limits, nothing a multiple of a tile
+    (4, 4, 1111, 333, 1001), (4, 2, 1111, 333, 1001), (8, 8, 901, 333, 1001),     # 128x128, three stages / six
+    (8, 8, 901, 2100, 1001),                                  # a long contraction on 128x128 (40 large tiles)
+    (4, 4, 12400, 650, 1001), (4, 4, 12400, 650, 1024),       # 128x256, five k-stages and a tail
+    (8, 8, 8500, 2100, 1041), (8, 8, 8500, 2100, 1040),       # 128x256 (306 large tiles), 32 stages and a tail
+    (4, 4, 28368, 1024, 3072),                                # fp32 on 128x256 although 128x128 deals 21 to 22
+]
+
+
+@pytest.mark.parametrize("bits_x,bits_w,M,K,Nout", TILED)
+def test_tiled_kernels_on_sampled_rows(bits_x, bits_w, M, K, Nout):
+    """The pipelined tiles with every stage refilled, ragged rows, channels and contraction, three runs each."""
+    rng = np.random.default_rng(M + 3 * K + 7 * Nout + bits_w)
+    lo_x, hi_x = vqo.qrange(bits_x)
+    lo_w, hi_w = vqo.qrange(bits_w)
+    xq = rng.integers(lo_x, hi_x + 1, (M, K), dtype=np.int8)
+    wq = rng.integers(lo_w, hi_w + 1, (Nout, K), dtype=np.int8)
+    s_w = np.exp(rng.uniform(-7, -4, Nout)).astype(np.float32)
+    bias = (rng.standard_normal(Nout) * 0.01).astype(np.float32)
+    s_x, s_y = np.float32(0.31), np.float32(0.2 if bits_x == 4 else 4.0)
+    xd, wd, swd, bd = to_qmat(xq, bits_x), to_qmat(wq, bits_w), dev(s_w), dev(bias)
+    # the first tile, rows on both sides of tile edges, some between, the last (partial) tile
+    rows = np.unique(np.r_[0:40, 120:136, 250:262, rng.integers(0, M, 40), M - 140:M])
+    at = torch.from_numpy(rows).cuda()
+    ref = vqo.linear(xq[rows], s_x, wq, s_w, bias=bias, s_y=s_y, bits_y=bits_x)
+    gelu = vqo.linear(xq[rows], s_x, wq, s_w, bias=bias, act=1, s_y=s_y, bits_y=bits_x)
+    assert len(np.unique(ref["yq"])) >= 8
+
+    def packed():
+        yq = vitq.QMat.empty(M, Nout, bits_x)
+        yq.data.fill_(0xFF)
+        return yq
+
+    for _ in range(3):
+        acc = torch.full((M, Nout), -7, dtype=torch.int32, device="cuda")
+        y, yf = torch.full((M, Nout), -7.0, device="cuda"), torch.full((M, Nout), -7.0, device="cuda")
+        q, qp, qg = packed(), packed(), packed()
+        vitq.vq_linear(xd, s_x, wd, swd, 1, bd, 0, acc, y, s_y, q)
+        vitq.vq_linear(xd, s_x, wd, swd, 1, bd, 0, None, yf, 0.0, None)
+        vitq.vq_linear(xd, s_x, wd, swd, 1, bd, 0, None, None, s_y, qp)
+        vitq.vq_linear(xd, s_x, wd, swd, 1, bd, 1, None, None, s_y, qg)
+        torch.cuda.synchronize()
+        assert np.array_equal(acc[at].cpu().numpy(), ref["acc"])
+        for got in (y, yf):
+            assert np.array_equal(got[at].cpu().numpy(), ref["y"])
+        for got, want in ((q, ref), (qp, ref), (qg, gelu)):
+            assert np.array_equal(got.data[at].cpu().numpy(), vqo.pack(want["yq"], storage_of(bits_x)))

@@ -112,9 +112,9 @@ def test_linear_shapes_and_bit_widths(bits_x, bits_w, M, K, Nout):
 
 @pytest.mark.parametrize("bits_x,bits_w", [(4, 4), (8, 8)])
 def test_long_contraction_single_output_kernels(bits_x, bits_w):
-    """K = 3072 over several token tiles with one output per call (the fp32-only and the packed-only
-    epilogues; 8-bit operands take their long-contraction tile configuration): every stage of the
-    software pipeline is refilled many times, and every element must be the oracle's."""
+    """K = 3072 with one output per call (the fp32-only and the packed-only epilogues) on few tokens: the
+    kernel that splits the contraction over a workgroup's waves, two rounds of six waves, and every
+    element must be the oracle's.  (The pipelined tiles at this length: test_gpu_linear_routes.py.)"""
     M, K, Nout = 600, 3072, 256
     rng = np.random.default_rng(3072 + bits_w)
     xq, wq, s_w, bias = _rand_case(rng, M, K, Nout, bits_x, bits_w)
