@@ -1311,10 +1311,13 @@ hipError_t launch(const GemmParams &p, hipStream_t stream) {
 
 template <int WB, int AB, int TC, int TT, int WAVES_C, int WAVES_T, int BK, int S, int OCC>
 hipError_t launch_epi(const GemmParams &p, int epi, hipStream_t stream) {
+    constexpr bool kGelu = !(WB == 4 && AB == 4 && TT == 256);      // (4-bit pairs with GELU: small_tile)
     switch (epi) {
         case kEpiF32: return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiF32>(p, stream);
         case kEpiQuant: return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiQuant>(p, stream);
-        case kEpiQuantGelu: return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiQuantGelu>(p, stream);
+        case kEpiQuantGelu:
+            if constexpr (kGelu) return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiQuantGelu>(p, stream);
+            return hipErrorInvalidValue;
         case kEpiHeadNorm: {
             // this epilogue keeps a token's whole 64-channel head in registers on top of the
             // accumulators: it runs with two waves per SIMD (256 registers) on 64x128 wave tiles
