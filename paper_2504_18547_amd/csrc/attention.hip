@@ -921,11 +921,14 @@ hipError_t launch_stream(const AttnParams &p, hipStream_t stream) {
     const size_t lds = (((size_t)nch * 64 * KPITCH + 15) & ~(size_t)15) + (size_t)64 * (nch * 64 + 16) +
                        (LUT ? (size_t)p.lut_n * 4 : 0);
     // Past half a CU's 160 KB a second workgroup would not fit, so the registers it would need are free for
-    // the exponentials (8-bit operands from 513 keys; 4-bit ones stay below and keep the occupancy, with
-    // which they measured the same).  Attention block, 8 bits, 577 keys: 9 images x 16 heads 144.7 -> 134.5 us,
-    // 64 x 12 496 -> 452; the 64-register form also spilled.
+    // the exponentials (8-bit operands from 513 keys, so the first KEEP tiles hold real keys only; 4-bit ones
+    // stay below and keep the occupancy, with which they measured the same).  Attention block, 8 bits, 577
+    // keys: 9 images x 16 heads 134 -> 126 us with P of 8 bits, 121 -> 116 with 4; 64 x 12 460 -> 420 and
+    // 432 -> 398 (513 to 592 keys, 1 to 64 images: 4 to 13 % everywhere).  With 128 registers 14 are spilled
+    // (P of 8 bits; 3 otherwise), with the 64 of the other form 18 (2).
     if constexpr (SB == 8) {
-        if (lds > 80 * 1024 && p.N >= 16 * KEEP) return launch_stream_keep<SB, P8, LUT, KEEP>(p, lds, stream);
+        static_assert(16 * KEEP <= 512, "kept tiles of real keys only");
+        if (lds > 80 * 1024) return launch_stream_keep<SB, P8, LUT, KEEP>(p, lds, stream);
     }
     return launch_stream_keep<SB, P8, LUT, 0>(p, lds, stream);
 }
@@ -933,7 +936,9 @@ hipError_t launch_stream(const AttnParams &p, hipStream_t stream) {
 template <int SB>
 hipError_t launch_stream_p(const AttnParams &p, hipStream_t stream) {
     if (p.pmax > 127) return launch_stream<SB, true, false>(p, stream);
-    if (SB == 4 && p.lut_n > 0) return launch_stream<SB, false, true>(p, stream);
+    if constexpr (SB == 4) {                              // (the table of exponentials is one of 4-bit operands)
+        if (p.lut_n > 0) return launch_stream<SB, false, true>(p, stream);
+    }
     return launch_stream<SB, false, false>(p, stream);
 }
 

@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 
 from oracle import vqo
 from paper_2504_18547_amd import vitq, workloads as wl
-from tests.gpu_util import assert_fp32_close, dev, device_weights, quantized_weights, storage_of
+from tests.gpu_util import assert_fp32_close, dev, device_weights, quantized_weights, storage_of, to_qmat
 
 
 def run_block_gpu(name, images, sharp, bits_w, bits_a, dumps=True, x_levels=None, wts=None, prepack=False):
@@ -82,6 +82,34 @@ def test_long_rows_take_the_streaming_attention(bits_w, bits_a, sharp):
     ref = compare_with_oracle(out, inp, bits_a, "tiny_long w%da%d" % (bits_w, bits_a))
     if sharp:
         assert len(np.unique(ref["o"])) >= 5
+
+
+@pytest.mark.parametrize("N,bits_p,B", [(512, 8, 1), (513, 8, 1), (513, 7, 1), (528, 8, 1), (576, 4, 1), (577, 8, 256),
+                                        (592, 8, 1), (592, 4, 1)])
+def test_streaming_attention_on_both_sides_of_513_keys(N, bits_p, B):
+    """8-bit operands: up to 512 keys two workgroups share a CU, from 513 on one keeps the exponentials of the
+    first sixteen key tiles in registers.  A whole last tile (528, 592), whole chunks (512, 576), P of 8, 7
+    and 4 bits; one image splits its queries over workgroups, 256 images do not (the last is compared)."""
+    bits, D, H = 8, 128, 2
+    dims = dict(D=D, H=H, N=N, hidden=0)
+    st = wl.block_steps("tiny_long", True, bits, bits)
+    wts = quantized_weights({k: v for k, v in wl.block_weights("tiny_long", sharp=True).items() if "fc" not in k}, bits)
+    wd = device_weights(wts, bits)
+    rng = np.random.default_rng(N + bits_p)
+    x = np.clip(np.rint(rng.standard_normal((B * N, D)) / float(st["s_x"])), -128, 127).astype(np.int8)
+    o = torch.zeros((B * N, D), dtype=torch.uint8, device="cuda")
+    desc = vitq.make_block_desc(dims, bits, bits_p, 8, wd, st, dict(o=o))
+    ws = torch.empty(vitq.vq_attention_block_workspace(desc, B), dtype=torch.uint8, device="cuda")
+    y = torch.full((B * N, D), -9.0, device="cuda")
+    for _ in range(3):
+        o.fill_(0x55)
+        vitq.vq_attention_block(desc, to_qmat(x, bits), B, y, ws)
+        torch.cuda.synchronize()
+        last = slice((B - 1) * N, B * N)
+        ref = vqo.attention_block(x[last], 1, dims, wts, st, bits_a=bits, bits_p=bits_p)
+        assert len(np.unique(ref["o"])) >= 20
+        assert np.array_equal(o[last].cpu().numpy().view(np.int8), ref["o"])
+        assert np.array_equal(y[last].cpu().numpy(), ref["y"])
 
 
 def test_paper_head_shape_n198():
