@@ -35,7 +35,7 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 // 1/k, k = 1 .. kRkMax, as hi + lo: hi = RN(1/k), lo = RN(1/k - hi), evaluated by the compiler.  Then
 //     t = RN(d*lo),  q = RN(d*hi + t)          (a multiply and an FMA)
 // equals RN(d/k) for every fp32 d with 2^-98 <= |d| and a finite result, and for d = 0: hi + lo and the
-// rounding of t are off by at most 2^-48 of the quotient together, while d/k is never the midpoint of two
+// rounding of t are off by at most 2^-48 of the quotient together (2^-39 where t is subnormal), while d/k is never the midpoint of two
 // neighbouring fp32 numbers (a midpoint has a 25-bit odd significand, which would have to divide the 24-bit
 // one of d) and never closer to one than 1/(2k) of their distance, i.e. 2^-37 of the quotient for
 // k <= 4096.  (tests/test_division_free_mean_update.py runs a slice of that space.)  An infinite or NaN d
