@@ -1361,8 +1361,8 @@ bool use_split(const GemmParams &p, int wb, int ab, int epi) {
 // deals the rows out more evenly (12,608 x 3072 -> 768: 300 large tiles leave two on some CUs and one on
 // most, 40.7 us; 594 small ones 34.4), where the tiles do not even fill the chip twice (6,304 rows of
 // the same: 26.4 -> 24.8 us; 12,608 x 384 -> 384 9.3 -> 9.0) and with the GELU epilogue, whose arithmetic
-// overlaps better with more independent workgroups (50,432 x 768 -> 3072: 170 -> 161 us).  On an even deal
-// the larger one reads less (6,304 x 768 -> 2304 in fp32 18.0 us against 18.2).
+// overlaps better with more independent workgroups (50,432 x 768 -> 3072: 166 -> 155 us).  On an even deal
+// the larger one reads less (12,608 x 4096 -> 1024 in fp32: 53.9 us against 55.6).
 // Large fp32 results of a long contraction are bound by their stores, and a deal that saves less than a
 // sixteenth does not make up for twice the tiles: 28,368 x 1024 -> 3072 113 us on large tiles, 121 on small
 // ones, 44,128 rows 181 and 190 (4096 channels: within 2 % either way).

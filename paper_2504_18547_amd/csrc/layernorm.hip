@@ -15,8 +15,9 @@
 // references (k - 1/2)*step that the normalised value exceeds, each decided as
 //     ssq((x - mu) * gamma) * n  >  ssq((k - 1/2)*step - beta) * V,      ssq(v) = v * |v|,
 // V = M_n + n*eps the (stabilised) sum of squared deviations -- sigma never appears.  Elements
-// are independent here, so the workgroup's rows are re-read (from L2) wave by wave with coalesced
-// 16-byte loads by all waves, four elements per lane, one row at a time, the next row in flight.  The comparisons are monotone in k, so
+// are independent here, so the workgroup's rows are re-read (from L2; rows of up to 128 columns from
+// LDS, where they still are) by all waves with coalesced 16-byte loads, four elements per lane, two to four
+// rows of a wave per pass.  The comparisons are monotone in k, so
 // instead of all 2^b - 1 of them the kernel makes a guess with the hardware reciprocal square
 // root.  A guess that lies further from every half-integer than the proven distance between the
 // guess and the comparator's own boundary stands as it is; otherwise the comparator itself is
@@ -35,10 +36,10 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 // 1/k, k = 1 .. kRkMax, as hi + lo: hi = RN(1/k), lo = RN(1/k - hi), evaluated by the compiler.  Then
 //     t = RN(d*lo),  q = RN(d*hi + t)          (a multiply and an FMA)
 // equals RN(d/k) for every fp32 d with 2^-98 <= |d| and a finite result, and for d = 0: hi + lo and the
-// rounding of t are off by at most 2^-48 of the quotient together (2^-39 where t is subnormal), while d/k is never the midpoint of two
-// neighbouring fp32 numbers (a midpoint has a 25-bit odd significand, which would have to divide the 24-bit
-// one of d) and never closer to one than 1/(2k) of their distance, i.e. 2^-37 of the quotient for
-// k <= 4096.  (tests/test_division_free_mean_update.py runs a slice of that space.)  An infinite or NaN d
+// rounding of t are off by at most 2^-48 of the quotient together (2^-39 where t is subnormal), while d/k is
+// never the midpoint of two neighbouring fp32 numbers (a midpoint has a 25-bit odd significand, which would
+// have to divide the 24-bit one of d) and never closer to one than 1/(2k) of their distance, i.e. 2^-37 of
+// the quotient for k <= 4096.  (tests/test_division_free_mean_update.py runs a slice of that space.)  An infinite or NaN d
 // gives a mean that is not finite from then on.
 constexpr int kRkMax = 4096;
 struct alignas(64) RkTable {       // (hi, lo) of 1/k at 2*(k - 1)
