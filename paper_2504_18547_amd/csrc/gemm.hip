@@ -1363,6 +1363,9 @@ bool use_split(const GemmParams &p, int wb, int ab, int epi) {
 // the same: 26.4 -> 24.8 us; 12,608 x 384 -> 384 9.3 -> 9.0) and with the GELU epilogue, whose arithmetic
 // overlaps better with more independent workgroups (50,432 x 768 -> 3072: 166 -> 155 us).  On an even deal
 // the larger one reads less (12,608 x 4096 -> 1024 in fp32: 53.9 us against 55.6).
+// (Of 129 to 160 rows the larger tile's second half is nearly empty and skips its epilogue, which the deal does
+// not see: the several-output epilogue, whose stores weigh most, keeps it there, 129 x 384 -> 20,000 24.1 us against
+// 31.5; GELU loses 3 to 18 % past 16,384 channels, too rare a call to build its kernel for that tile.)
 // Large fp32 results of a long contraction are bound by their stores, and a deal that saves less than a
 // sixteenth does not make up for twice the tiles: 28,368 x 1024 -> 3072 113 us on large tiles, 121 on small
 // ones, 44,128 rows 181 and 190 (4096 channels: within 2 % either way).
@@ -1393,6 +1396,7 @@ bool small_tile(const GemmParams &p, int epi) {
         return (p.M > 160 || long_k) && channels * (4 * p.ab_nthr + 3 * p.K / 4) <= (long_k ? 4000000 : 3000000);
     }
     if (epi == kEpiAbsorbed) return cs < cl;
+    if (epi == kEpiGeneric && p.M > 128 && p.M <= 160) return false;
     if (epi == kEpiF32 && p.K >= 1024 && cl > 16) return false;
     return epi == kEpiQuantGelu || cs < cl || cs <= 2;
 }

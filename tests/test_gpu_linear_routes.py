@@ -76,6 +76,7 @@ TILED = [
     (4, 4, 12400, 650, 1001), (4, 4, 12400, 650, 1024),       # 128x256, five k-stages and a tail
     (8, 8, 8500, 2100, 1041), (8, 8, 8500, 2100, 1040),       # 128x256 (306 large tiles), 32 stages and a tail
     (4, 4, 28368, 1024, 3072),                                # fp32 on 128x256 although 128x128 deals 21 to 22
+    (4, 4, 150, 333, 7001),                                   # several outputs of 129 to 160 rows: 128x256, else 128x128
 ]
 
 
@@ -93,6 +94,7 @@ def test_tiled_kernels_on_sampled_rows(bits_x, bits_w, M, K, Nout):
     xd, wd, swd, bd = to_qmat(xq, bits_x), to_qmat(wq, bits_w), dev(s_w), dev(bias)
     # the first tile, rows on both sides of tile edges, some between, the last (partial) tile
     rows = np.unique(np.r_[0:40, 120:136, 250:262, rng.integers(0, M, 40), M - 140:M])
+    rows = rows[(rows >= 0) & (rows < M)]
     at = torch.from_numpy(rows).cuda()
     ref = vqo.linear(xq[rows], s_x, wq, s_w, bias=bias, s_y=s_y, bits_y=bits_x)
     gelu = vqo.linear(xq[rows], s_x, wq, s_w, bias=bias, act=1, s_y=s_y, bits_y=bits_x)
