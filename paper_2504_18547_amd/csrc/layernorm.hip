@@ -25,6 +25,7 @@
 // every decision is the comparator's.
 #include "layernorm.h"
 #include <type_traits>
+#include "launch_util.h"
 #include "vitq_dev.h"
 
 namespace vitq {
@@ -78,6 +79,60 @@ __device__ __forceinline__ float2 ln_walk_row(const float *xr, const float *rr, 
     return make_float2(mu, m2);
 }
 
+// Levels of columns c0 .. c0 + 3 of a row by the comparator, one byte each, biased by -qmin.  level = qmin +
+// #{lv : above(lv)}; above() is monotone in lv, so c is the level iff above(c) (or c == qmin) and not above(c + 1) (or
+// c == qmax).  st: mean, guess of 1/(sigma*step), -, V.  from_sum: the row is what sum_out holds already.
+__device__ __forceinline__ u32 ln_compare(const LnParams &p, int64_t row, int c0, const float4 &st, float rstep, bool from_sum) {
+    const int cols = (int)p.cols;
+    const float nf = (float)cols, V = st.w, qminf = (float)p.qmin, qmaxf = (float)p.qmax;
+    float L[4], bt[4], lv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int c = min(c0 + i, cols - 1);
+        const int64_t at = row * p.ld + c;
+        const float x = from_sum ? p.sum_out[at] : (p.res ? p.x[at] + p.res[at] : p.x[at]);
+        const float a = x - st.x;
+        const float g = a * p.gamma[c];
+        bt[i] = p.beta[c];
+        const float gs = g * fabsf(g);
+        L[i] = gs * nf;
+        lv[i] = fminf(fmaxf(rintf(fmaf(g, st.y, bt[i] * rstep)), qminf), qmaxf);             // (NaN: qmin)
+    }
+    auto above = [&](int i, float k) {                    // comparator of Fig. 5(b)
+        const float rk = (k - 0.5f) * p.step;
+        const float cc = rk - bt[i];
+        const float cs = cc * fabsf(cc);
+        const float rhs = cs * V;
+        return L[i] > rhs;
+    };
+    for (int it = 0; it <= p.qmax - p.qmin; ++it) {
+        bool moved = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool low_ok = (lv[i] <= qminf) || above(i, lv[i]);
+            const bool high_ok = (lv[i] >= qmaxf) || !above(i, lv[i] + 1.0f);
+            const float d = !low_ok ? -1.0f : (!high_ok ? 1.0f : 0.0f);
+            lv[i] = lv[i] + d;
+            moved = moved || d != 0.0f;
+        }
+        if (__builtin_amdgcn_ballot_w64(moved) == 0) break;
+    }
+    u32 w = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w |= (u32)(int)(lv[i] - qminf) << (8 * i);
+    return w;
+}
+
+// What the level pass needs of a row: mean, guess of 1/(sigma*step), 0 (or infinity: no guess), V.  In a row whose V is
+// not an ordinary number every element is compared.
+__device__ __forceinline__ float4 ln_row_stats(const LnParams &p, float mu, float m2, float rstep) {
+    const float nf = (float)(int)p.cols;
+    const float ne = nf * p.eps;
+    const float V = m2 + ne;
+    const bool plain = V >= 0x1p-40f && V <= 0x1p30f && p.step >= 0x1p-20f && p.step <= 0x1p10f;
+    return make_float4(mu, __builtin_amdgcn_rsqf(V / nf) * rstep, plain ? 0.0f : __uint_as_float(0x7F800000u), V);
+}
+
 // R rows per workgroup: see layernorm_quantize_launch.
 // SHORT: rows of at most kXBufs chunks (128 columns).  There the level pass is what bounds the call: three
 // round trips to memory for rows that LDS still holds, and 8 to 32 of a wave's 64 lanes at work.  So the rows
@@ -100,7 +155,6 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t row0 = (int64_t)blockIdx.x * R;
     const int cols = (int)p.cols;
-    const float nf = (float)cols;
 
     // ---- phase 1: Eq. 5, mu_i = mu_{i-1} + (x_i - mu_{i-1}) / i,
     //                     M_i  = M_{i-1}  + (x_i - mu_{i-1}) * (x_i - mu_i)
@@ -371,11 +425,7 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
             mu = st.x;
             m2 = st.y;
         }
-        const float ne = nf * p.eps;
-        const float V = m2 + ne;
-        // in a row whose V is not an ordinary number every element is compared
-        const bool plain = V >= 0x1p-40f && V <= 0x1p30f && p.step >= 0x1p-20f && p.step <= 0x1p10f;
-        s_row[lane] = make_float4(mu, __builtin_amdgcn_rsqf(V / nf) * rstep, plain ? 0.0f : __uint_as_float(0x7F800000u), V);
+        s_row[lane] = ln_row_stats(p, mu, m2, rstep);
     }
     __syncthreads();
 
@@ -470,53 +520,377 @@ __global__ __launch_bounds__(kLnWaves * 64, 6) void layernorm_quantize_kernel(Ln
                 }
             });
         });
-        // Rare: items with an element inside the guard.  level = qmin + #{lv : above(lv)}; above() is monotone in
-        // lv, so c is the level iff above(c) (or c == qmin) and not above(c + 1) (or c == qmax).
+        // Rare: items with an element inside the guard.
         while (redo) {
             const int item = __builtin_ctz(redo);
             redo &= redo - 1;
             const int c0 = 4 * gl + (SHORT ? 0 : 256 * (pass / HALVES * BL + item / NB)), r = row_of(pass, item % NB);
             if (c0 >= padded || r >= nrows) continue;
             const float4 st = s_row[r];
-            const float V = st.w;
-            const int c[4] = {c0, min(c0 + 1, cols - 1), min(c0 + 2, cols - 1), min(c0 + 3, cols - 1)};
-            float L[4], bt[4], lv[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int64_t at = (row0 + r) * p.ld + min(c[i], cols - 1);
-                const float x = MODE != kLnVec && p.sum_out ? p.sum_out[at] : (p.res ? p.x[at] + p.res[at] : p.x[at]);
-                const float a = x - st.x;
-                const float g = a * p.gamma[min(c[i], cols - 1)];
-                bt[i] = p.beta[min(c[i], cols - 1)];
-                const float gs = g * fabsf(g);
-                L[i] = gs * nf;
-                lv[i] = fminf(fmaxf(rintf(fmaf(g, st.y, bt[i] * rstep)), qminf), qmaxf);             // (NaN: qmin)
-            }
-            auto above = [&](int i, float k) {            // comparator of Fig. 5(b)
-                const float rk = (k - 0.5f) * p.step;
-                const float cc = rk - bt[i];
-                const float cs = cc * fabsf(cc);
-                const float rhs = cs * V;
-                return L[i] > rhs;
-            };
-            for (int it = 0; it <= p.qmax - p.qmin; ++it) {
-                bool moved = false;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const bool low_ok = (lv[i] <= qminf) || above(i, lv[i]);
-                    const bool high_ok = (lv[i] >= qmaxf) || !above(i, lv[i] + 1.0f);
-                    const float d = !low_ok ? -1.0f : (!high_ok ? 1.0f : 0.0f);
-                    lv[i] = lv[i] + d;
-                    moved = moved || d != 0.0f;
-                }
-                if (__builtin_amdgcn_ballot_w64(moved) == 0) break;
-            }
-            u32 w = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) w |= (u32)(int)(lv[i] - qminf) << (8 * i);
+            const u32 w = ln_compare(p, row0 + r, c0, st, rstep, MODE != kLnVec && p.sum_out);
             store_levels(r, c0, w);
         }
     }
+}
+
+// ---- rows of 129 to 1152 columns without a residual: the workgroup's rows stay in registers -------------------
+// One workgroup of sixteen waves per CU.  Twelve of them request all of the workgroup's rows at once and keep them,
+// NP 16-byte pieces per lane, so that the level pass reads no memory, and the even deal of the rows over the CUs
+// (up to R = 16, 32 or 64 of them: a wave's lanes walk one each) leaves no second round of workgroups half empty.
+// What bounds the call is then the walker's chain, four dependent instructions per column of 4.3 cycles each, and
+// everything else is kept off that wave, which issues an instruction per 4.3 cycles whatever it is: the operands of
+// the next sixteen columns (row pieces from LDS, 1/i from scalar memory) are requested before the current sixteen
+// are walked, and only every fourth mean leaves it, in one 16-byte write per sixteen columns (a wave that does nothing
+// else: 17.4 cycles per column; with the reads 19.7, with the scalar loads 20.6, with all means written 27.4,
+// with every fourth 22.5).  The lane that holds a piece repeats its four steps.
+// A chunk is 1024 / R columns = 256 pieces, one per lane of a set of four loading waves; the three sets take the
+// chunks in turn.  In step t chunk t is walked, the set of chunk t + 3 puts it into LDS, that of chunk t - 1 multiplies
+// its deviations, and the adder sums the products of chunk t - 2 up in order.
+// A chunk in LDS: 16-byte group c (four columns) of row r at c * (R + 1) + r.
+// us per call, fp32 -> 4 bits, kernel above / this: 768 columns 197 rows 21.3 / 15.1, 4,096 21.6 / 15.2, 9,900 28.4 / 20.8,
+// 12,608 32.3 / 22.0 (of it the walk 10.6, levels 4.1), 16,384 33.6 / 26.2; 384 columns 197 rows 13.0 / 10.0, 9,900
+// 16.7 / 13.3; 1,024 columns 12,608 rows 40.0 / 29.4.
+constexpr int kResWaves = 16, kResSets = 3;
+constexpr int kResMaxCols = 1152;
+// LDS: per-column parameters of the level pass, then the chunks, over which the packed rows are laid once they are done with
+template <int R>
+constexpr size_t kResRings = (size_t)6 * (256 / R) * (R + 1) * 16 + 4 * 1024;
+template <int R>
+size_t resident_lds(const LnParams &p) {
+    const size_t groups = ((size_t)p.cols + 1024 / R - 1) / (1024 / R) * (256 / R), rows = (size_t)R * (p.row_bytes16 + 16);
+    return groups * 68 + (rows > kResRings<R> ? rows : kResRings<R>) + 16;
+}
+template <int SB, int R, int NP>
+__global__ __launch_bounds__(kResWaves * 64, 4) void layernorm_resident_kernel(LnParams p, int wg_rows) {
+    constexpr int CH = 1024 / R, G = CH / 4, BPC = CH / 16, CQ = G * (R + 1);
+    static_assert(R * G == 256 && CH % 16 == 0 && kResMaxCols <= kRkMax, "one piece per lane of a set");
+    extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];
+    __shared__ __attribute__((aligned(16))) float4 s_row[R];
+    __shared__ float s_m2[R];                             // sum of squared deviations
+    __shared__ u32 s_least[R];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t row0 = (int64_t)blockIdx.x * wg_rows;
+    const int nrows = (int)min((int64_t)wg_rows, p.rows - row0);
+    const int cols = (int)p.cols;
+    const int nch = (cols + CH - 1) / CH;
+    float4 *const s_gm = reinterpret_cast<float4 *>(s_dyn), *const s_bt = s_gm + nch * G;     // gamma, beta (see below) of four columns
+    float4 *const s_rk = s_bt + nch * G;                                                      // their (hi, lo) of 1/i: two each
+    float *const s_limit = reinterpret_cast<float *>(s_rk + 2 * nch * G);
+    float4 *const s_x = reinterpret_cast<float4 *>(s_dyn + ((nch * G * 68 + 15) & ~15));      // [4] chunks of rows
+    float4 *const s_end = s_x + 4 * CQ;                   // [4] chunks: per batch and row, the mean after columns 4, 8, 12, 16
+    float4 *const s_p = s_end + 4 * BPC * R;              // [2] chunks of products
+    const float rstep = __builtin_amdgcn_rcpf(p.step);    // for the guess only
+    const float qminf = (float)p.qmin;
+    const float top = (float)p.qmax - qminf;
+    float mu = 0.0f, m2 = 0.0f;
+    // The rows of the workgroup, as the loading waves hold them: piece i of a lane is group g of chunk 3 * i + set.
+    const int set = (wave >> 2) - 1;
+    const int lt = (wave & 3) * 64 + lane;
+    const int row = lt / G, g = lt % G;
+    float4 x[NP];
+
+    // Every wave passes the same nch + 4 barriers: behind the first three chunks, once more, and behind each of the
+    // nch + 2 steps.
+    const int steps = nch + 2;
+    if (wave == 0) {
+        if (lane < R) {
+            __builtin_amdgcn_s_setprio(3);
+            s_end[(3 * BPC + BPC - 1) * R + lane].w = 0.0f;                   // the mean before chunk 0
+            __syncthreads();
+            typedef __attribute__((address_space(4))) const v16f const_v16f;  // (constant memory: scalar loads)
+            uint64_t rk = reinterpret_cast<uint64_t>(g_rk.v);
+            asm("" : "+s"(rk));                           // (one address computation, not one per load)
+            struct Batch { float4 x[4]; v16f k[2]; };     // sixteen columns: row pieces and (hi, lo) of 1/i
+            Batch even, odd;
+            auto fill = [&](int b, Batch &n) {
+                const float4 *src = s_x + ((b / BPC) & 3) * CQ + (b % BPC) * 4 * (R + 1) + lane;
+                const const_v16f *t = reinterpret_cast<const const_v16f *>(rk) + 2 * b;
+                n.k[0] = t[0];
+                n.k[1] = t[1];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) n.x[i] = src[i * (R + 1)];
+            };
+            auto walk4 = [&](const Batch &n, auto I) {
+                constexpr int i = decltype(I)::value;
+                const float e[4] = {n.x[i].x, n.x[i].y, n.x[i].z, n.x[i].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float d1 = e[j] - mu;
+                    const float tq = d1 * n.k[i >> 1][8 * (i & 1) + 2 * j + 1];
+                    mu = mu + fmaf(d1, n.k[i >> 1][8 * (i & 1) + 2 * j], tq);
+                }
+                return mu;
+            };
+            // One batch.  The barrier ahead of a chunk's step stands behind the first four columns of the chunk, and the
+            // wait for the next batch's operands ahead of the last write: LDS and scalar loads share a counter that can
+            // only be waited to zero, and all that it then waits for was sent off twelve columns earlier.
+            auto batch = [&](int b, auto FIRST, const Batch &cur, Batch &next) {
+                constexpr bool first = decltype(FIRST)::value;                // of its chunk
+                const int c = b / BPC;
+                float end[4];
+                static_for<4>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    end[i] = walk4(cur, I);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (i == 0) {
+                        if constexpr (first) __syncthreads();
+                        fill(b + 1, next);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                });
+                __builtin_amdgcn_s_waitcnt(0xC07F);       // lgkmcnt(0)
+                __builtin_amdgcn_sched_barrier(0);
+                s_end[((c & 3) * BPC + b % BPC) * R + lane] = make_float4(end[0], end[1], end[2], end[3]);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            using T = std::true_type;
+            using F = std::false_type;
+            const int fast = cols / CH;                   // whole chunks
+            int c = 0;
+            fill(0, even);
+            __builtin_amdgcn_s_waitcnt(0xC07F);           // (here, so that the loop's head does not wait for the writes before it)
+            if constexpr (BPC == 1) {
+                for (; c + 2 <= fast; c += 2) {
+                    batch(c, T{}, even, odd);
+                    batch(c + 1, T{}, odd, even);
+                }
+                if (c < fast) batch(c++, T{}, even, odd);
+            } else {
+                for (; c < fast; ++c) {
+                    const int b = c * BPC;
+                    batch(b, T{}, even, odd);
+                    batch(b + 1, F{}, odd, even);
+                    if constexpr (BPC == 4) {
+                        batch(b + 2, F{}, even, odd);
+                        batch(b + 3, F{}, odd, even);
+                    }
+                }
+            }
+            if (c < nch) {                                // the columns' end inside a chunk
+                __syncthreads();
+                const int n = cols - c * CH;
+                for (int j = 0; j < n / 16; ++j) {
+                    fill(c * BPC + j, even);
+                    float end[4];
+                    static_for<4>([&](auto I) { end[decltype(I)::value] = walk4(even, I); });
+                    s_end[((c & 3) * BPC + j) * R + lane] = make_float4(end[0], end[1], end[2], end[3]);
+                }
+                float *dst = reinterpret_cast<float *>(s_end + (c & 3) * BPC * R + lane);
+                const float *src = reinterpret_cast<const float *>(s_x + (c & 3) * CQ + lane);
+                for (int i = n & ~15; i < n; ++i) {
+                    const float2 k = *reinterpret_cast<const float2 *>(g_rk.v + 2 * (c * CH + i));
+                    const float d1 = src[(i >> 2) * 4 * (R + 1) + (i & 3)] - mu;
+                    const float tq = d1 * k.y;
+                    mu = mu + fmaf(d1, k.x, tq);
+                    dst[(i >> 4) * 4 * R + ((i >> 2) & 3)] = mu;              // (the last one of four columns stays)
+                }
+            }
+            __builtin_amdgcn_s_setprio(0);
+            for (int t = 0; t < 3; ++t) __syncthreads();
+        }
+    } else if (wave == 1) {
+        const int lr = min(lane, R - 1);
+        for (int t = 0; t < 4; ++t) __syncthreads();
+        for (int c = 0; c < nch; ++c) {
+            const float4 *src = s_p + (c & 1) * CQ + lr;
+            const int n = min(cols - c * CH, CH);
+            if (n == CH) {
+                float4 v[2][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[0][i] = src[i * (R + 1)];
+#pragma unroll
+                for (int j = 0; j < BPC; ++j) {
+                    if (j + 1 < BPC) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[(j + 1) & 1][i] = src[(4 * (j + 1) + i) * (R + 1)];
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float4 &a = v[j & 1][i];
+                        m2 = m2 + a.x; m2 = m2 + a.y; m2 = m2 + a.z; m2 = m2 + a.w;
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                for (int i = 0; i < n; ++i) m2 = m2 + reinterpret_cast<const float *>(src)[(i >> 2) * 4 * (R + 1) + (i & 3)];
+            }
+            __syncthreads();
+        }
+        if (lane < R) s_m2[lane] = m2;
+    } else if (wave < 4) {
+        // The guess of a level, tp = g * (rs*rstep) + beta*rstep, and the distance from every half-integer that makes
+        // it the comparator's, are derived at the kernel above; the parts that depend on the column only are laid
+        // out here for all rows: gamma, beta in steps (4-bit fields: counted from -qmin) and the limit.
+        if (wave == 2) {
+            for (int r = lane; r < R; r += 64) s_least[r] = 0xFFFFFFFFu;
+        }
+        for (int q = (wave & 1) * 64 + lane; q < 2 * nch * G; q += 128) s_rk[q] = reinterpret_cast<const float4 *>(g_rk.v)[q];
+        __syncthreads();
+        for (int q = (wave & 1) * 64 + lane; q < nch * G; q += 128) {
+            float gm[4], bt[4], btr[4], bmax = 0.0f, odd = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                gm[i] = p.gamma[min(4 * q + i, cols - 1)];
+                bt[i] = p.beta[min(4 * q + i, cols - 1)];
+                btr[i] = SB == 8 ? bt[i] * rstep : fmaf(bt[i], rstep, -qminf);
+                bmax = fmaxf(bmax, fabsf(bt[i] * rstep));
+                odd = odd + (gm[i] - gm[i]) + (bt[i] - bt[i]);           // NaN unless all of them are finite
+            }
+            s_gm[q] = make_float4(gm[0], gm[1], gm[2], gm[3]);
+            s_bt[q] = make_float4(btr[0], btr[1], btr[2], btr[3]);
+            s_limit[q] = (0.5f - kLnGuard * (3.0f * bmax + (SB == 8 ? 3.0f : 39.0f))) + odd;
+        }
+        for (int t = 0; t < steps + 1; ++t) __syncthreads();
+    } else {
+        // (columns and rows beyond the matrix: clamped, not used)
+        const float *src = p.x + (row0 + min(row, nrows - 1)) * p.ld;
+        // A set would otherwise request all of its chunks before the next set requests its first.
+        constexpr int PD = NP < 5 ? NP : 5;
+        auto request = [&](auto I) {
+            constexpr int i = decltype(I)::value;
+            if constexpr (i < NP)
+                x[i] = *reinterpret_cast<const float4 *>(src + min((kResSets * i + set) * CH + 4 * g, cols - 4));
+        };
+        static_for<PD>([&](auto I) { request(I); });
+        const int at = g * (R + 1) + row;
+        // the mean before a piece: what the walker left four columns earlier (of the chunk before, for the first piece)
+        const float *ends = reinterpret_cast<const float *>(s_end + row);
+        const int before_at = g == 0 ? ((BPC - 1) * R * 4 + 3) : ((g - 1) >> 2) * R * 4 + ((g - 1) & 3);
+        u32 least = 0xFFFFFFFFu;                          // twice the bits of the smallest nonzero deviation, minus one
+        s_x[set * CQ + at] = x[0];
+        __syncthreads();
+        __syncthreads();
+        int t = 0;
+        for (; t < set; ++t) __syncthreads();
+        // Three steps of the set at a time: chunk t + 3 = piece j + 1 is put, chunk t = piece j multiplied one step later.
+        // (Nested rather than in sequence: no path joins another one, so the compiler counts the loads in flight.)
+        auto three_steps = [&](auto &&self, auto J) __attribute__((always_inline)) -> void {
+            constexpr int j = decltype(J)::value;
+            if (t >= steps) return;
+            if constexpr (j + 1 < NP) s_x[((t + 3) & 3) * CQ + at] = x[j + 1];
+            request(std::integral_constant<int, j + PD>{});
+            __syncthreads();
+            if (t + 1 >= steps) return;
+            if constexpr (j < NP) {
+                const float4 v = x[j], k0 = s_rk[2 * (t * G + g)], k1 = s_rk[2 * (t * G + g) + 1];
+                float m = ends[((g == 0 ? t - 1 : t) & 3) * BPC * R * 4 + before_at];
+                const float e[4] = {v.x, v.y, v.z, v.w}, hi[4] = {k0.x, k0.z, k1.x, k1.z}, lo[4] = {k0.y, k0.w, k1.y, k1.w};
+                float pr[4];
+                u32 l[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float d1 = e[i] - m;
+                    const float tq = d1 * lo[i];
+                    m = m + fmaf(d1, hi[i], tq);
+                    const float d2 = e[i] - m;
+                    pr[i] = d1 * d2;
+                    l[i] = (__float_as_uint(d1) << 1) - 1u;                      // (zero wraps to the largest value)
+                }
+                s_p[(t & 1) * CQ + at] = make_float4(pr[0], pr[1], pr[2], pr[3]);
+                const u32 l4 = min(min(l[0], l[1]), min(l[2], l[3]));
+                if (t * CH + 4 * g < cols) least = min(least, l4);
+            }
+            __syncthreads();
+            if (t + 2 >= steps) return;
+            __syncthreads();
+            t += kResSets;
+            if constexpr (j < NP) self(self, std::integral_constant<int, j + 1>{});
+        };
+        three_steps(three_steps, std::integral_constant<int, 0>{});
+        atomicMin(&s_least[row], least);
+    }
+    __syncthreads();
+    if (wave == 0 && lane < nrows) {
+        m2 = s_m2[lane];
+        // (a deviation too small for the two-step quotient, or anything that is not finite: divide)
+        const bool ok = fabsf(mu) <= 3.0e38f && s_least[lane] >= 2u * __float_as_uint(kRkMinDev) - 1u;
+        if (!ok) {
+            const float2 st = ln_walk_row(p.x + (row0 + lane) * p.ld, nullptr, cols);
+            mu = st.x;
+            m2 = st.y;
+        }
+        s_row[lane] = ln_row_stats(p, mu, m2, rstep);
+    }
+    __syncthreads();
+
+    // ---- levels, into packed rows over the chunks' LDS, and from there to memory in whole 16-byte pieces ----
+    uint8_t *const s_out = reinterpret_cast<uint8_t *>(s_x);
+    const int pitch = p.row_bytes16 + 16;                 // (spreads the rows over the banks)
+    if (wave >= 4 && row < nrows) {
+        const u32 unbias = (u32)(p.qmin & ((1 << SB) - 1)) * 0x01010101u;    // added per byte: level - qmin -> field
+        auto store_levels = [&](int q, u32 w) {
+            uint8_t *dst = s_out + row * pitch + q * (4 * SB / 8);
+            if constexpr (SB == 8) {
+                *reinterpret_cast<u32 *>(dst) = ((w & 0x7F7F7F7Fu) + (unbias & 0x7F7F7F7Fu)) ^ ((w ^ unbias) & 0x80808080u);
+            } else {
+                w = (w + unbias) & 0x0F0F0F0Fu;
+                *reinterpret_cast<uint16_t *>(dst) = (uint16_t)__builtin_amdgcn_perm(0u, w | (w >> 4), 0x0C0C0200u);
+            }
+        };
+        const float4 st = s_row[row];
+        u32 redo = 0;                                     // pieces with an element inside the guard
+        static_for<NP>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            const int q = (kResSets * i + set) * G + g;   // this piece's group of four columns
+            if (4 * q < cols) {
+                const float4 gm = s_gm[q], bt = s_bt[q];
+                const float e[4] = {x[i].x, x[i].y, x[i].z, x[i].w}, gi[4] = {gm.x, gm.y, gm.z, gm.w}, bi[4] = {bt.x, bt.y, bt.z, bt.w};
+                float tp[4], d[4];
+                u32 w = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float a = e[k] - st.x;
+                    const float gg = a * gi[k];
+                    tp[k] = fmaf(gg, st.y, bi[k]);
+                    d[k] = tp[k] - rintf(tp[k]);
+                    // (to nearest even, saturates to a byte; 8-bit fields: rounded first, adding the bias would round again)
+                    const float lv = SB == 8 ? fminf(rintf(tp[k]) - qminf, top) : __builtin_amdgcn_fmed3f(tp[k], 0.0f, top);
+                    w = __builtin_amdgcn_cvt_pk_u8_f32(lv, k, w);
+                }
+                float fig = fmaxf(fmaxf(fmaxf(fabsf(d[0]), fabsf(d[1])), fabsf(d[2])), fabsf(d[3])) + st.z;
+                if constexpr (SB == 8)
+                    fig = fmaf(fmaxf(fmaxf(fmaxf(fabsf(tp[0]), fabsf(tp[1])), fabsf(tp[2])), fabsf(tp[3])), 4.0f * kLnGuard, fig);
+                if (!(fig <= s_limit[q])) redo |= 1u << i;
+                store_levels(q, w);
+            }
+        });
+        while (__builtin_amdgcn_ballot_w64(redo != 0) != 0) {                   // (rare)
+            if (redo != 0) {
+                const int i = __builtin_ctz(redo);
+                redo &= redo - 1;
+                const int q = (kResSets * i + set) * G + g;
+                store_levels(q, ln_compare(p, row0 + row, 4 * q, st, rstep, false));
+            }
+        }
+    }
+    __syncthreads();
+    const int pieces = p.row_bytes16 / 16, live = cols * SB / 8;              // of a row; its bytes without the padding
+    for (int r = wave; r < nrows; r += kResWaves)
+        for (int i = lane; i < pieces; i += 64) {
+            uint4 v = *reinterpret_cast<const uint4 *>(s_out + r * pitch + 16 * i);
+            const int over = 16 * (i + 1) - live;         // bytes of padding in this piece: zeros
+            if (over > 0) {
+                auto word = [&](u32 w, int last) {        // last: bytes of the piece behind this word
+                    const int pad = over - last;
+                    return pad <= 0 ? w : (pad >= 4 ? 0u : w & (0xFFFFFFFFu >> (8 * pad)));
+                };
+                v = make_uint4(word(v.x, 12), word(v.y, 8), word(v.z, 4), word(v.w, 0));
+            }
+            *reinterpret_cast<uint4 *>(p.out + (row0 + r) * p.out_stride + 16 * i) = v;
+        }
+}
+
+template <int SB, int R, int NP>
+hipError_t launch_resident(const LnParams &p, int wg_rows, hipStream_t stream) {
+    auto kern = layernorm_resident_kernel<SB, R, NP>;
+    const size_t lds = resident_lds<R>(p);
+    static std::atomic<uint64_t> allowed{0};              // (one per instantiation)
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), 128 * 1024, allowed);
+    if (e != hipSuccess) return e;
+    const unsigned blocks = (unsigned)((p.rows + wg_rows - 1) / wg_rows);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kResWaves * 64), lds, stream, p, wg_rows);
+    return hipGetLastError();
 }
 
 // ---- per-head LayerNorm quantizer of Q and K, plain quantizer of V (Fig. 1(b), Table I) --------
@@ -636,6 +1010,27 @@ hipError_t layernorm_quantize_launch(const LnParams &p, hipStream_t stream) {
     if (p.rows == 0) return hipSuccess;
     const bool vec = (p.cols % 4 == 0) && (p.ld % 4 == 0) && (((uintptr_t)p.x) % 16 == 0) &&
                      (!p.res || ((uintptr_t)p.res) % 16 == 0) && (!p.sum_out || ((uintptr_t)p.sum_out) % 16 == 0);
+    // Rows that stay in registers (see layernorm_resident_kernel), as long as one round of workgroups takes them all: its
+    // workgroup fills a CU, so a second round would begin when the first is through, and the kernel above, whose
+    // workgroups overlap, is ahead or even there (18,000 x 384 20 us against 23, 25,216 x 768 40 and 41, 50,432 x 132 20 and 29).
+    // At least four rows, one per SIMD in the level pass: with one row or sixteen 197 x 768 takes as long or 0.6 us more.
+    constexpr int64_t kCUs = 256;
+    if (vec && !p.res && !p.sum_out && (p.sb == 4 || p.sb == 8) && p.cols > kXBufs * kLnCols && p.cols <= kResMaxCols &&
+        p.rows <= 64 * kCUs) {
+        const int wg_rows = (int)max((int64_t)4, (p.rows + kCUs - 1) / kCUs);
+        auto launch_pieces = [&](auto SB, auto ROWS) {
+            constexpr int sb = decltype(SB)::value, R = decltype(ROWS)::value, unit = R / 8;
+            if (p.cols <= kResMaxCols / 3) return launch_resident<sb, R, unit>(p, wg_rows, stream);
+            if (p.cols <= 2 * kResMaxCols / 3) return launch_resident<sb, R, 2 * unit>(p, wg_rows, stream);
+            return launch_resident<sb, R, 3 * unit>(p, wg_rows, stream);
+        };
+        auto launch_rows = [&](auto SB) {
+            if (wg_rows <= 16) return launch_pieces(SB, std::integral_constant<int, 16>{});
+            if (wg_rows <= 32) return launch_pieces(SB, std::integral_constant<int, 32>{});
+            return launch_pieces(SB, std::integral_constant<int, 64>{});
+        };
+        return p.sb == 4 ? launch_rows(std::integral_constant<int, 4>{}) : launch_rows(std::integral_constant<int, 8>{});
+    }
     // Rows per workgroup.  The recurrences take the same time for 16 rows as for 64 (a lane is a row); fewer rows
     // leave a wave fewer of them in the level pass and bring more CUs in, as long as every workgroup is resident:
     // three per CU (80 registers, 21 waves), so 12,288 and 24,576 rows are where one more round would begin.

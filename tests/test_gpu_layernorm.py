@@ -268,3 +268,40 @@ def test_short_rows_side_by_side(rows, cols, bits):
     torch.cuda.synchronize()
     assert np.array_equal(out.data.cpu().numpy(), vqo.pack(ref["q"], storage_of(bits)))
     assert np.array_equal(xd.cpu().numpy(), ref["sum"])
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("cols", [132, 384, 388, 500, 768, 772, 1152, 1156])      # pieces per lane, chunk ends, the longest row
+@pytest.mark.parametrize("rows", [3, 197, 1025])
+def test_rows_that_stay_in_registers(rows, cols, bits):
+    """Rows of up to 1152 columns held by the loading waves: whole and partial chunks, workgroups cut short, a row of every
+    kind that leaves the fast paths (tiny, huge, constant, not finite), columns on a boundary (the comparator)."""
+    rng = np.random.default_rng(rows + 1000 * cols + bits)
+    x, gamma, beta = _case(rng, rows, cols)
+    step = np.float32(2.5 / vqo.qrange(bits)[1])
+    gamma[::7], beta[::7] = 0.0, step * np.float32(0.5)
+    x[0, cols - 1] = 1e4
+    x[1] *= 1e-36
+    x[2] = 0.75
+    if rows > 100:
+        x[60], x[77, 33], x[90, 1:] = x[60] * 1e37, np.nan, 0.0
+    _check(x, gamma, beta, 1e-6, step, bits)
+
+
+@pytest.mark.parametrize("rows,cols", [(4096, 132), (4097, 260), (8192, 196), (8193, 132), (16384, 132), (16385, 132)])
+def test_rows_per_workgroup_of_the_one_round_form(rows, cols):
+    """The sizes at which its lanes per walking wave change (16, 32, 64 rows per CU) and where it ends, rows at any distance."""
+    rng = np.random.default_rng(rows + cols)
+    x, gamma, beta = _case(rng, rows, cols)
+    _check(x, gamma, beta, 1e-6, np.float32(0.4), 4)
+    _check(x[:3000], gamma, beta, 0.0, np.float32(0.02), 8, ld=None)
+    big = torch.zeros((rows, cols + 12), device="cuda")
+    big[:, :cols] = dev(x)
+    out = vitq.QMat.empty(rows, cols, 4, row_stride=(cols // 2 + 15) // 16 * 16 + 32)
+    out.data.fill_(0x5A)
+    vitq.vq_layernorm_quantize(big[:, :cols], None, None, dev(gamma), dev(beta), 1e-6, 0.4, out)
+    torch.cuda.synchronize()
+    row_bytes = (cols // 2 + 15) // 16 * 16
+    got = out.data.cpu().numpy()
+    want = vqo.pack(vqo.layernorm_quantize(x, gamma, beta, 1e-6, np.float32(0.4), 4)["q"], 4)
+    assert np.array_equal(got[:, :row_bytes], want[:, :row_bytes]) and (got[:, row_bytes:] == 0x5A).all()
