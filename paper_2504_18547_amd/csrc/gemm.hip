@@ -916,6 +916,7 @@ void gemm_kernel(GemmParams p) {
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
+    if constexpr (!(WB == 8 && AB == 8)) {
     sync_stage(0);
     load_raw(0, I0{});
     unpack(I0{}, I0{});
@@ -973,6 +974,54 @@ void gemm_kernel(GemmParams p) {
     };
     for (int kt = 0; kt < nk - 1; ++kt) kstep(kt, std::true_type{});
     kstep(nk - 1, std::false_type{});
+    } else {
+        // 8-bit operands need no unpacking: a step of 32 values is one 16-byte read per operand block,
+        // straight into the fragment set that the next step's matrix instructions take.
+        constexpr int NST = BK / 32;
+        auto read_step = [&](int buf, auto ST, auto FB) {
+            constexpr int ss = decltype(ST)::value / 2, j = decltype(ST)::value % 2, fb = decltype(FB)::value;
+            const uint8_t *stage = smem + buf * STAGE;
+#pragma unroll
+            for (int ci = 0; ci < NC; ++ci) wf[fb][ci] = *reinterpret_cast<const v4i *>(stage + w_rd[ss][j % WRD] + ci * 32 * WROW);
+#pragma unroll
+            for (int ti = 0; ti < NTK; ++ti) xf[fb][ti] = *reinterpret_cast<const v4i *>(stage + x_rd[ss][j % XRD] + ti * 32 * XROW);
+        };
+        auto steps = [&](int kt, auto NEXT_) {
+            constexpr bool NEXT = decltype(NEXT_)::value;
+            static_for<NST>([&](auto ST) {
+                constexpr int st = decltype(ST)::value, fb = st & 1;
+                using FB = std::integral_constant<int, fb>;
+                using OTHER = std::integral_constant<int, fb ^ 1>;
+                constexpr bool more = st + 1 < NST;
+                pin(FB{});
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (st == 0) {
+                    if (kt >= 1 && kt + S - 1 < nk) {
+                        issue_part(kt + S - 1, I1{});
+                        if constexpr (NST == 2) issue_part(kt + S - 1, std::integral_constant<int, 2>{});
+                    }
+                }
+                if constexpr (st == 1 && NST > 2) {
+                    if (kt >= 1 && kt + S - 1 < nk) issue_part(kt + S - 1, std::integral_constant<int, 2>{});
+                }
+                if constexpr (!more && NEXT) sync_stage(kt + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (more) read_step(kt % S, std::integral_constant<int, (more ? st + 1 : 0)>{}, OTHER{});
+                else if constexpr (NEXT) read_step((kt + 1) % S, I0{}, OTHER{});
+                mma(FB{});
+#pragma unroll
+                for (int i = 0; i < kMma; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    if constexpr (more || NEXT) __builtin_amdgcn_sched_group_barrier(0x100, (NC + NTK + kMma - 1) / kMma, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        };
+        sync_stage(0);
+        read_step(0, I0{}, I0{});
+        for (int kt = 0; kt < nk - 1; ++kt) steps(kt, std::true_type{});
+        steps(nk - 1, std::false_type{});
+    }
     __syncthreads();
 
 
@@ -1309,15 +1358,23 @@ hipError_t launch(const GemmParams &p, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// the epilogues with one output and whole 16-channel groups (fp32: any width)
+template <int WB, int AB, int TC, int TT, int WAVES_C, int WAVES_T, int BK, int S, int OCC>
+hipError_t launch_main(const GemmParams &p, int epi, hipStream_t stream) {
+    constexpr bool kGelu = !(WB == 4 && AB == 4 && TT == 256);      // (4-bit pairs with GELU: small_tile)
+    if (epi == kEpiF32) return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiF32>(p, stream);
+    if (epi == kEpiQuant) return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiQuant>(p, stream);
+    if constexpr (kGelu) {
+        if (epi == kEpiQuantGelu) return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiQuantGelu>(p, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
 template <int WB, int AB, int TC, int TT, int WAVES_C, int WAVES_T, int BK, int S, int OCC>
 hipError_t launch_epi(const GemmParams &p, int epi, hipStream_t stream) {
-    constexpr bool kGelu = !(WB == 4 && AB == 4 && TT == 256);      // (4-bit pairs with GELU: small_tile)
     switch (epi) {
-        case kEpiF32: return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiF32>(p, stream);
-        case kEpiQuant: return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiQuant>(p, stream);
-        case kEpiQuantGelu:
-            if constexpr (kGelu) return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiQuantGelu>(p, stream);
-            return hipErrorInvalidValue;
+        case kEpiF32: case kEpiQuant: case kEpiQuantGelu:
+            return launch_main<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC>(p, epi, stream);
         case kEpiHeadNorm: {
             // this epilogue keeps a token's whole 64-channel head in registers on top of the
             // accumulators: it runs with two waves per SIMD (256 registers) on 64x128 wave tiles
@@ -1401,6 +1458,46 @@ bool small_tile(const GemmParams &p, int epi) {
     return epi == kEpiQuantGelu || cs < cl || cs <= 2;
 }
 
+// 8-bit pairs: which tile?  kSmall: 128x128, 64 values per k-stage, three stages, three workgroups per CU.  kDeep: 128
+// values per stage, two stages, two workgroups.  kLarge: 256x256 on sixteen waves, 128 values, two stages, one.  A
+// stage of 64 values is half a cache line of every operand row, which L2 then sends twice, and a barrier every eight
+// MFMAs of a wave; the larger tile reads half the bytes per product but has no other workgroup beside its epilogue (GELU's
+// most of all).  What decides is the busiest CU's work in units of 128x128, times what the form takes per unit.  us of
+// kSmall / kDeep / kLarge, outputs fp32 (f), requantized (q), GELU (g), calls repeated until the clock is steady, in
+// parentheses the units of the small tiles and of the large one:
+//   (1, 4)  5,193 x 1024 -> 1024 q 13.8 / 12.5 / 17 (up to two units: kDeep is ahead or level everywhere)
+//   (3, 4)  12,608 x 3072 -> 768 f 48.5 / 46.2 / 38.2, q 49.4 / 48.4 / 38.6, g 52.1 / 52.7 / 45.3; K 768 f 18.1 / 19.9 / 16.9,
+//           q 17.9 / 18.9 / 16.6, g 22.3 / 23.1 / 24.4; 25,216 x 384 -> 384 f 12.8 / 14.1 / 13.4; x 1536 g 31.6 / 34.2 / 33.9
+//   (4, 4)  12,608 x 384 -> 1152 f 18.7 / 17.2 / 16.9, q 17.5 / 17.2 / 15.4, g 23.0 / 23.7 / 23.5
+//   (5, 8)  25,216 x 3072 -> 768 f 86.2 / 74.3 / 81.7, q 83.4 / 77.4 / 82.8, g 87.1 / 83.7 / 97.3
+//   (7, 8)  6,304 x 1024 -> 4096 q, with its quantizer 51.3 / - / 45.4; 12,608 x 768 -> 2304 f 42.0 / 44.8 / 39.2, q 39.6 / 40.8 / 36.2,
+//           g 46.3 / 50.5 / 51.8
+//   (10, 12)  12,608 x 768 -> 3072 f 57.1 / 61.6 / 59.6, q 51.3 / 53.3 / 55.0, g 60.9 / 64.0 / 75.1
+//   (14, 16)  25,216 x 768 -> 2304 f 89.6 / 90.9 / 79.9, q 74.5 / 75.7 / 73.2, g 85.5 / 90.6 / 98.6; x 384 -> 1152 (7, 8)
+//           q 27.3 / 29.9 / 28.3
+//   (25, 28)  25,216 x 4096 -> 1024 f 150 / 127 / 113, q 149 / 130 / 111, g 152 / 136 / 123
+//   (74, 76)  25,216 x 1024 -> 3072 f 147 / 143 / 121, q 118 / 120 / 107, g 136 / 140 / 142
+// A dense kernel that holds the chip for long also holds its clock down for the kernels around it: in the ViT-B block of
+// 128 images, calls in a row, kLarge for its QKV linear (14, 16) and kDeep for its fc2 (5, 8) cost the block 376 -> 400 us
+// although each saves 1 to 12 us by itself, the attention between them going from 72 to 77.  So kLarge has to be ahead by
+// a twelfth past eight units (the figures below contain it), and kDeep is for calls too small to matter (one at a time, 25,216 x 3072 -> 768
+// 161.5 us with its quantizer on kSmall, 163.7 on kDeep; 25,216 x 1024 -> 3072 143 on kSmall, 132 on kLarge).  The 128x256
+// tile on four waves that long contractions took before is behind by 2 to 25 % wherever it ran.
+enum class Tile8 { kSmall, kDeep, kLarge };
+Tile8 tile8(const GemmParams &p, int epi) {
+    constexpr int64_t kCUs = 256;
+    const int64_t small = (int64_t)((p.Nout + 127) / 128) * (((int64_t)p.M + 127) / 128);
+    const int64_t large = (int64_t)((p.Nout + 255) / 256) * (((int64_t)p.M + 255) / 256);
+    const int64_t cs = (small + kCUs - 1) / kCUs, cl = 4 * ((large + kCUs - 1) / kCUs);       // units of the busiest CU
+    const bool gelu = epi == kEpiQuantGelu, one_round = large <= kCUs;
+    if (cs <= 2) return Tile8::kDeep;
+    int unit;                                       // of kLarge, in hundredths of kSmall's
+    if (p.K >= (gelu ? 2304 : 1536)) unit = gelu && !one_round ? 76 : 65;
+    else if (p.K >= 768) unit = one_round ? (gelu ? 82 : 65) : (gelu ? 108 : (cs <= 8 ? 84 : 91));
+    else unit = gelu ? 108 : (one_round ? 82 : (epi == kEpiF32 ? 95 : 104));
+    return unit * cl < 100 * cs ? Tile8::kLarge : Tile8::kSmall;
+}
+
 }  // namespace
 
 hipError_t gemm_launch(GemmParams p, int wb, int ab, hipStream_t stream) {
@@ -1455,16 +1552,11 @@ hipError_t gemm_launch(GemmParams p, int wb, int ab, hipStream_t stream) {
     }
     if (wb == 2 && ab == 4) return launch_epi<2, 4, 128, 128, 2, 2, 128, 2, 4>(p, epi, stream);
     if (wb == 8 && ab == 8) {
-        // 8-bit operands are read from LDS at twice the bytes per product and need no unpacking: a long
-        // contraction is bound by those reads and gains from 64x128 wave tiles (a quarter fewer fragment
-        // reads per product, at two waves per SIMD); a short one is dominated by its epilogue, which wants
-        // four waves per SIMD.  With no more large tiles than CUs it is the walk of K by one workgroup that
-        // takes the time, and halving the tile halves it (5,193 x 4096 -> 1024: 168 large tiles, 47.0 ->
-        // 38.5 us; 16,384 x 2048 -> 512: 256, 30.1 -> 27.9); beyond that the larger one is ahead
-        // (9,900 x 4096 -> 1024: 312, 59.2 us against 65.2; 25,216 x 2048 -> 512: 396, 38.3 against 49.0).
-        const int64_t large = (int64_t)((p.Nout + 127) / 128) * (((int64_t)p.M + 255) / 256);
-        if (p.K >= 2048 && large > 256 && (epi == kEpiF32 || epi == kEpiQuant || epi == kEpiQuantGelu))
-            return launch_epi<8, 8, 128, 256, 2, 2, 64, 3, 2>(p, epi, stream);
+        if (epi == kEpiF32 || epi == kEpiQuant || epi == kEpiQuantGelu) {
+            const Tile8 tile = tile8(p, epi);
+            if (tile == Tile8::kLarge) return launch_main<8, 8, 256, 256, 4, 4, 128, 2, 4>(p, epi, stream);
+            if (tile == Tile8::kDeep) return launch_main<8, 8, 128, 128, 2, 2, 128, 2, 2>(p, epi, stream);
+        }
         return launch_epi<8, 8, 128, 128, 2, 2, VITQ_BK88, VITQ_S88, VITQ_OCC88>(p, epi, stream);
     }
     if (wb == 8 && ab == 4) return launch_epi<8, 4, VITQ_TC, VITQ_TT, VITQ_WC, VITQ_WT, VITQ_BK84, VITQ_S84, VITQ_OCC84>(p, epi, stream);

@@ -23,7 +23,7 @@ CASES = [
     (8, 8, 800, 200, 896), (8, 8, 801, 200, 896),                         # 700, 728
     (8, 8, 32, 8193, 16448),                                              # 514 blocks of more than 128 MB: tiled
     (4, 4, 12797, 40, 1024), (4, 4, 8445, 40, 1024),                      # 128x256 tiles (an even deal), 128x128
-    (8, 8, 35, 2049, 32912), (8, 8, 35, 2049, 32768),                     # 258 large tiles, 256
+    (8, 8, 35, 2049, 32912), (8, 8, 35, 2049, 32768),                     # 258 tiles, 256
 ]
 
 
@@ -72,9 +72,9 @@ def test_linear_route(bits_x, bits_w, M, K, Nout):
 TILED = [
     # bits_x, bits_w, M, K, Nout: past the split kernel's limits, nothing a multiple of a tile
     (4, 4, 1111, 333, 1001), (4, 2, 1111, 333, 1001), (8, 8, 901, 333, 1001),     # 128x128, three stages / six
-    (8, 8, 901, 2100, 1001),                                  # a long contraction on 128x128 (40 large tiles)
+    (8, 8, 901, 2100, 1001),                                  # a long contraction on 128x128
     (4, 4, 12400, 650, 1001), (4, 4, 12400, 650, 1024),       # 128x256, five k-stages and a tail
-    (8, 8, 8500, 2100, 1041), (8, 8, 8500, 2100, 1040),       # 128x256 (306 large tiles), 32 stages and a tail
+    (8, 8, 8500, 2100, 1041), (8, 8, 8500, 2100, 1040),       # 256x256 (170 tiles), 16 stages and a tail
     (4, 4, 28368, 1024, 3072),                                # fp32 on 128x256 although 128x128 deals 21 to 22
     (4, 4, 150, 333, 7001),                                   # several outputs of 129 to 160 rows: 128x256, else 128x128
 ]
@@ -119,3 +119,17 @@ def test_tiled_kernels_on_sampled_rows(bits_x, bits_w, M, K, Nout):
             assert np.array_equal(got[at].cpu().numpy(), ref["y"])
         for got, want in ((q, ref), (qp, ref), (qg, gelu)):
             assert np.array_equal(got.data[at].cpu().numpy(), vqo.pack(want["yq"], storage_of(bits_x)))
+
+
+@pytest.mark.parametrize("M,K,Nout", [
+    (8500, 200, 1040), (8500, 65, 1040),      # three small tiles on some CUs, a short contraction: 64 values per stage
+    (16300, 333, 1024), (16300, 333, 1000),   # one even round of 256x256 but for GELU; ragged channels
+    (4133, 800, 2064), (4133, 768, 2064),     # 153 tiles of 256x256 (GELU: 128x128), with a tail and without
+    (4133, 640, 2064),                        # the same of a short contraction: 64 values per stage
+    (6304, 800, 4096),                        # 400 tiles of 256x256 for 1,600 small ones (GELU: those)
+    (8193, 2400, 2048),                       # 264 for 1,040: two rounds do not pay
+    (16384, 128, 2048), (16385, 2400, 256),   # two even rounds, one stage; a tile of one row and one of 256 channels
+])
+def test_eight_bit_tiles(M, K, Nout):
+    """Each 8-bit tile on both sides of the rule that picks it."""
+    test_tiled_kernels_on_sampled_rows(8, 8, M, K, Nout)
