@@ -100,6 +100,31 @@ def test_irregular_reference_tables():
     assert np.all(ref["yq"][:, 1] == -3)
 
 
+@pytest.mark.parametrize("bits_w,bits_a,bits_y,M,Nout", [
+    (4, 4, 4, 300, 272), (4, 4, 3, 130, 144), (2, 4, 4, 130, 144), (8, 8, 4, 130, 144), (4, 4, 2, 40, 16)])
+def test_evenly_spaced_references_and_where_that_ends(bits_w, bits_a, bits_y, M, Nout):
+    """Tables with a constant spacing, sums on and next to the references; then one channel of the first tile at every bound
+    of what counts as even: the spacing, a reference off its place, the distance from the bias, the first one far away."""
+    xq, wq, _, _ = _operands(31 + Nout, M, 160, Nout, bits_w, bits_a)
+    rng = np.random.default_rng(32)
+    n = (1 << bits_y) - 1
+    wide = 8 if bits_a == 8 else 1
+    gaps = rng.choice([4, 5, 16, 37, 60], Nout) * wide
+    b_int = rng.integers(-50, 50, Nout).astype(np.int32)
+    thr = ((np.arange(n)[None, :] - n // 2) * gaps[:, None] + rng.integers(-9, 9, Nout)[:, None]).astype(np.int32)
+    sums = xq.astype(np.int64) @ wq.astype(np.int64).T + b_int
+    for c in range(0, Nout, 5):
+        thr[c] += np.int32(sums[c % M, c] - thr[c, c % n])             # a reference that some sum equals
+    _run(xq, wq, b_int, thr, bits_w, bits_a, bits_y)
+    up = np.arange(n)
+    for channel in (up * 3, up * 4 + (up == 1), up * 8 + 3 * (up == 1), up * 8 + 4 * (up == 1), up * 16 - 7 * (up == n // 2),
+                    2 ** 22 - 9 * n + up * 8, 2 ** 22 - 7 * n + up * 8, 2 ** 20 - 7 * n + up * 8, -2 ** 22 - 1 + up * 8,
+                    2 ** 31 - 1 - up[::-1] * 8, -2 ** 31 + up * 8, -2 ** 22 + up * (2 ** 23 // n)):
+        some = thr.copy()
+        some[7] = np.asarray(channel, np.int64).astype(np.int32)
+        _run(xq, wq, b_int, some, bits_w, bits_a, bits_y)
+
+
 def test_equivalent_bias_at_the_int32_limits():
     """b_int is clamped to int32 by the preparation step, so a near-dead channel carries INT32_MAX or
     INT32_MIN; the sum with an accumulator of the same sign then leaves 32 bits, and the oracle
