@@ -388,12 +388,15 @@ __device__ __forceinline__ void epilogue_quant(const GemmParams &p, const v16i &
 // provably far from every boundary, and otherwise picks which two comparisons are evaluated.
 // The fp32 linear output never leaves registers.
 // gamma / beta / the folded scales are wave-uniform: staged in LDS once per tile and read as
-// broadcasts.
+// broadcasts.  tmp: this lane's column of 32 x 64 floats in LDS.
+// Bound by VALU issue at two waves per SIMD.  9,900 tokens x 384 -> 1152, 2-bit weights: 28.7 us with a division per element
+// and a verification branch per level, 22.9 with the quotients below and one test per eight levels (though the
+// rare paths' control flow makes the compiler spill part of the other token blocks' accumulators).
 constexpr float kHnGuard = 0x1p-21f;   // unit of the guard that lets a guessed level stand (see the LayerNorm kernel)
 template <int SB, int NTK, int PAIR>   // PAIR: token blocks 2*PAIR and 2*PAIR + 1 of the wave's NTK
 __device__ __forceinline__ void epilogue_headnorm(const GemmParams &p, v16i (&acc)[2][NTK], int shift, uint8_t *dst,
                                                   const float *scs64, const float *bs64, float step,
-                                                  const float *gp, const float *bp) {
+                                                  const float *gp, const float *bp, float *tmp) {
     // trade halves: afterwards sw[0] is channel 32*ci + r and sw[1] channel 32*ci + 16 + r of this
     // lane's token.  The definition's y = fma((float)acc, s_x*s_w[c], b[c]); the caller passes
     // either the folded scales (which carry 2^-shift exactly) with shift 0, or the plain ones.
@@ -409,72 +412,124 @@ __device__ __forceinline__ void epilogue_headnorm(const GemmParams &p, v16i (&ac
         }
         __builtin_amdgcn_sched_barrier(0);   // the two accumulator tiles are dead before the next pair is touched
     }
+    // The running mean's division by a constant is a multiply and an FMA (a multiply where it is a power of two) with
+    // 1/i as a sum hi + lo of two fp32 numbers: the bits of the IEEE quotient for a deviation of zero or at least 2^-98 and
+    // a finite mean (proof at the LayerNorm kernel's table).  Any other token is walked again with divisions.
     float mu = 0.0f, m2 = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 64; ++i) {
+    u32 least = 0xFFFFFFFFu;                                 // twice the bits of the smallest nonzero deviation, minus one
+    static_for<64>([&](auto I) {
+        constexpr int i = decltype(I)::value, k = i + 1;
+        constexpr float hi = 1.0f / (float)k, lo = (float)((1.0 - (double)hi * (double)k) / (double)k);
         const float d1 = v[i] - mu;
-        mu = mu + d1 / (float)(i + 1);
+        if constexpr ((k & (k - 1)) == 0) {
+            mu = mu + d1 * hi;
+        } else {
+            const float tq = d1 * lo;
+            mu = mu + fmaf(d1, hi, tq);
+            least = min(least, (__float_as_uint(d1) << 1) - 1u);         // (zero wraps to the largest value)
+        }
         const float d2 = v[i] - mu;
         const float pr = d1 * d2;
         m2 = m2 + pr;
+    });
+    const bool walked = fabsf(mu) <= 3.0e38f && least >= 2u * __float_as_uint(0x1p-98f) - 1u;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!walked) != 0, 0)) {
+        // (rare; from LDS and rolled up, so that its divisions cost the others no registers)
+        mu = 0.0f;
+        m2 = 0.0f;
+        static_for<2>([&](auto H) {
+            constexpr int h = decltype(H)::value;
+#pragma unroll
+            for (int i = 0; i < 32; ++i) tmp[64 * i] = v[32 * h + i];
+#pragma unroll 1
+            for (int i = 0; i < 32; ++i) {
+                const float x = tmp[64 * i];
+                const float d1 = x - mu;
+                mu = mu + d1 / (float)(32 * h + i + 1);
+                const float d2 = x - mu;
+                const float pr = d1 * d2;
+                m2 = m2 + pr;
+            }
+        });
     }
     const float nf = 64.0f;
     const float ne = nf * p.hn_eps;
     const float V = m2 + ne;
-    const float rs = __builtin_amdgcn_rsqf(V / nf);          // for the guess only
     const float rstep = __builtin_amdgcn_rcpf(step);         // for the guess only
+    const float rsr = __builtin_amdgcn_rsqf(V / nf) * rstep; // for the guess only
     const bool stats_ok = step >= 0x1p-20f && step <= 0x1p10f && V >= 0x1p-40f && V <= 0x1p30f;
     const float qminf = p.qminf, qmaxf = p.qmaxf;
     const int span = (int)(qmaxf - qminf);
     const float bias8 = -qminf;
+    // The guess tp is within (|g/(sigma*step)| + |beta/step|) * 2^-21 of the exact-arithmetic value the
+    // comparator tests, and the comparator's own fp32 evaluation moves a boundary by at most
+    // (2|level| + |beta/step| + 1) * 2^-22: a guess further than 2^-21 * (4|tp| + 3|beta/step| + 3) from every
+    // half-integer is the level the comparator would count, and it is not run (stats_ok: the squares stay
+    // ordinary numbers, which that error model needs).  Eight channels share one test, with the largest |beta/step|
+    // of theirs; the figures are compared as bit patterns, where a NaN is above everything and fails it.
+    // Levels leave biased, 0 .. qmax - qmin, one byte each: w8[2*j], w8[2*j + 1] hold channels 8*j .. 8*j + 7.
+    u32 w8[16];
+    static_for<8>([&](auto J) {
+        constexpr int j = decltype(J)::value;
+        float lv[8];
+        u32 worst = 0u, bmax = 0u;
 #pragma unroll
-    for (int i = 0; i < 64; ++i) {
-        const float gm = gp[i], bt = bp[i];
-        const float a = v[i] - mu;
-        const float g = a * gm;
-        const float gs = g * fabsf(g);
-        const float L = gs * nf;
-        auto above = [&](float k) {
-            const float rk = (k - 0.5f) * step;
-            const float cc = rk - bt;
-            const float cs = cc * fabsf(cc);
-            const float R = cs * V;
-            return L > R;
-        };
-        // The guess tp is within (|g/(sigma*step)| + |beta/step|) * 2^-21 of the exact-arithmetic value the
-        // comparator tests, and the comparator's own fp32 evaluation moves a boundary by at most
-        // (2|level| + |beta/step| + 1) * 2^-22: a guess further than 2^-21 * (4|tp| + 3|beta/step| + 3) from every
-        // half-integer is the level the comparator would count, and it is not run (stats_ok: the squares stay
-        // ordinary numbers, which that error model needs).  A NaN figure fails the test and is verified.
-        const float tp = fmaf(g, rs, bt) * rstep;
-        const float tt = rintf(tp);
-        float c = (tt == tt) ? __builtin_amdgcn_fmed3f(tt, qminf, qmaxf) : qminf;
-        const float cgi = fmaf(fabsf(bt * rstep), 3.0f * kHnGuard, 3.0f * kHnGuard);
-        const float fig = fmaf(fabsf(tp), 4.0f * kHnGuard, fabsf(tp - tt)) + cgi;
-        if (!(stats_ok && fig <= 0.5f)) {
-            for (int it = 0; it <= span; ++it) {
-                const bool low_ok = (c <= qminf) || above(c);
-                const bool high_ok = (c >= qmaxf) || !above(c + 1.0f);
-                if (low_ok && high_ok) break;
-                c = c + (!low_ok ? -1.0f : 1.0f);
+        for (int r = 0; r < 8; ++r) {
+            const int i = 8 * j + r;
+            const float btr = bp[i] * rstep;
+            const float g = (v[i] - mu) * gp[i];
+            const float tp = fmaf(g, rsr, btr);
+            const float tt = rintf(tp);
+            worst = max(worst, __float_as_uint(fmaf(fabsf(tp), 4.0f * kHnGuard, fabsf(tp - tt))));
+            bmax = max(bmax, __float_as_uint(fabsf(btr)));
+            lv[r] = __builtin_amdgcn_fmed3f(tt, qminf, qmaxf);
+        }
+        const float fig = __uint_as_float(worst) + fmaf(__uint_as_float(bmax), 3.0f * kHnGuard, 3.0f * kHnGuard);
+        const bool sure = stats_ok && fig <= 0.5f;
+        if (__builtin_amdgcn_ballot_w64(!sure) != 0) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const int i = 8 * j + r;
+                const float bt = bp[i];
+                const float a = v[i] - mu;
+                const float g = a * gp[i];
+                const float gs = g * fabsf(g);
+                const float L = gs * nf;
+                auto above = [&](float k) {
+                    const float rk = (k - 0.5f) * step;
+                    const float cc = rk - bt;
+                    const float cs = cc * fabsf(cc);
+                    const float R = cs * V;
+                    return L > R;
+                };
+                float c = (lv[r] == lv[r]) ? fminf(fmaxf(lv[r], qminf), qmaxf) : qminf;
+                for (int it = 0; it <= span; ++it) {
+                    const bool low_ok = (c <= qminf) || above(c);
+                    const bool high_ok = (c >= qmaxf) || !above(c + 1.0f);
+                    if (low_ok && high_ok) break;
+                    c = c + (!low_ok ? -1.0f : 1.0f);
+                }
+                lv[r] = c;
             }
         }
-        v[i] = c + bias8;                                  // stored biased: 0 .. qmax - qmin
-        if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-    }
+        u32 ev = 0, od = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            // 4 bits: even and odd channels apart, as the nibbles are merged; 8 bits: in order
+            ev = __builtin_amdgcn_cvt_pk_u8_f32(lv[SB == 4 ? 2 * r : r] + bias8, r, ev);
+            od = __builtin_amdgcn_cvt_pk_u8_f32(lv[SB == 4 ? 2 * r + 1 : 4 + r] + bias8, r, od);
+        }
+        w8[2 * j] = ev;
+        w8[2 * j + 1] = od;
+        __builtin_amdgcn_sched_barrier(0);
+    });
     if (!dst) return;
     if constexpr (SB == 4) {
         const u32 fix = 0x11111111u * ((u32)bias8 & 0xFu);
         u32 w[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            u32 ev = 0, od = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                ev = __builtin_amdgcn_cvt_pk_u8_f32(v[8 * j + 2 * i], i, ev);
-                od = __builtin_amdgcn_cvt_pk_u8_f32(v[8 * j + 2 * i + 1], i, od);
-            }
-            const u32 a0 = ev | (od << 4);
+            const u32 a0 = w8[2 * j] | (w8[2 * j + 1] << 4);
             w[j] = ((a0 | 0x88888888u) - (fix & 0x77777777u)) ^ ((a0 ^ ~fix) & 0x88888888u);
         }
         *reinterpret_cast<uint4 *>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
@@ -486,9 +541,7 @@ __device__ __forceinline__ void epilogue_headnorm(const GemmParams &p, v16i (&ac
             u32 w[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                u32 x = 0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) x = __builtin_amdgcn_cvt_pk_u8_f32(v[16 * q + 4 * j + i], i, x);
+                const u32 x = w8[4 * q + j];
                 w[j] = ((x | 0x80808080u) - (fix & 0x7F7F7F7Fu)) ^ ((x ^ ~fix) & 0x80808080u);
             }
             *reinterpret_cast<uint4 *>(dst + 16 * q) = make_uint4(w[0], w[1], w[2], w[3]);
@@ -1154,14 +1207,16 @@ void gemm_kernel(GemmParams p) {
                 const float *sc64 = (fold_ok ? s_scs : s_raw) + wave_c * WC;
                 const int sh = fold_ok ? 0 : shift;
                 if constexpr (EPI == kEpiHeadNorm) {
+                    static_assert(WAVES_C * WAVES_T * 8192 <= S * STAGE, "the pipeline buffers hold what a wave walks again");
+                    float *tmp = reinterpret_cast<float *>(smem) + wave * 2048 + lane;
                     static_for<NTK / 2>([&](auto PI) {
                         constexpr int pair = decltype(PI)::value;
                         const int64_t tk = packed_token_part(p, t0 + wave_t * WT + 64 * pair + 32 * g + li);
                         uint8_t *dst = (ch_part >= 0 && tk >= 0) ? p.yq + tk + ch_part : nullptr;
                         if (p.yq_sb == 4)
-                            epilogue_headnorm<4, NTK, pair>(p, acc, sh, dst, sc64, s_bs + wave_c * WC, step, s_hg + wave_c * WC, s_hb + wave_c * WC);
+                            epilogue_headnorm<4, NTK, pair>(p, acc, sh, dst, sc64, s_bs + wave_c * WC, step, s_hg + wave_c * WC, s_hb + wave_c * WC, tmp);
                         else
-                            epilogue_headnorm<8, NTK, pair>(p, acc, sh, dst, sc64, s_bs + wave_c * WC, step, s_hg + wave_c * WC, s_hb + wave_c * WC);
+                            epilogue_headnorm<8, NTK, pair>(p, acc, sh, dst, sc64, s_bs + wave_c * WC, step, s_hg + wave_c * WC, s_hb + wave_c * WC, tmp);
                     });
                 }
                 return;

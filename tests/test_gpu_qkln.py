@@ -212,3 +212,44 @@ def test_fused_epilogue_values_planted_on_both_sides_of_the_guard():
     for i, nm in enumerate("qkv"):
         assert np.array_equal(qkv[i], ref[nm]), "%s levels differ (%d)" % (nm, (qkv[i] != ref[nm]).sum())
     assert np.array_equal(y.cpu().numpy(), ref["y"])
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+def test_fused_epilogue_tokens_whose_mean_needs_the_division(bits):
+    """Deviations below 2^-98 (down to subnormal ones) and heads that are not finite, beside ordinary heads and tokens: with
+    zero QKV weights the linear's output is its bias.  Also a head that is tiny first and ordinary later."""
+    dims = dict(D=256, H=4, N=37, hidden=0)
+    D, H, N, B = 256, 4, 37, 3
+    lo, hi = vqo.qrange(bits)
+    sa = storage_of(bits)
+    rng = np.random.default_rng(78 + bits)
+    b = (rng.standard_normal(3 * D) * 1.5 + 0.3).astype(np.float32)
+    b[0:64] *= np.float32(2.0 ** -105)
+    b[64:128] = (rng.integers(-40, 40, 64) * 2.0 ** -149).astype(np.float32)
+    b[128:144] *= np.float32(2.0 ** -110)
+    b[D + 10], b[D + 64 + 62], b[D + 128 + 63], b[D + 192:D + 256] = np.inf, np.nan, -np.inf, 0.0
+    wts = quantized_weights(wl.block_weights("tiny_attn", sharp=True), bits)
+    w = {"w_qkv": np.zeros((3 * D, D), np.int8), "sw_qkv": np.full(3 * D, 0.01, np.float32), "b_qkv": b,
+         "w_proj": rng.integers(lo, hi + 1, (D, D)).astype(np.int8), "sw_proj": np.full(D, 0.01, np.float32),
+         "b_proj": np.zeros(D, np.float32)}
+    assert set(k for k in wts if k.endswith("qkv")) == {"w_qkv", "sw_qkv", "b_qkv"}
+    ln = _ln(D)
+    ln["beta"][::9] = 0.0
+    steps = dict(s_x=0.5, s_q=np.float32(2.5 / hi), s_k=np.float32(3.0 / hi), s_v=np.float32(3.0 / hi), s_o=0.1, scale=0.125)
+    wd = device_weights(w, bits)
+    x = rng.integers(lo, hi + 1, (B * N, D)).astype(np.int8)
+    dump = {"qkv": torch.zeros((3 * B * H * N, 64 * sa // 8), dtype=torch.uint8, device="cuda")}
+    desc = vitq.make_block_desc(dims, bits, bits, sa, wd, steps, dump,
+                                qkln=dict(gamma=dev(ln["gamma"]), beta=dev(ln["beta"]), eps=ln["eps"]))
+    ws = torch.empty(vitq.vq_attention_block_workspace(desc, B), dtype=torch.uint8, device="cuda")
+    y = torch.empty((B * N, D), dtype=torch.float32, device="cuda")
+    xd = vitq.QMat.empty(B * N, D, bits)
+    xd.data.copy_(torch.from_numpy(vqo.pack(x, sa)))
+    vitq.vq_attention_block(desc, xd, B, y, ws)
+    torch.cuda.synchronize()
+    qkv = vqo.unpack(dump["qkv"].cpu().numpy(), 64, sa).reshape(3, B, H, N, 64)
+    for which, step in ((0, steps["s_q"]), (1, steps["s_k"])):
+        for h in range(H):
+            sl = slice(which * D + h * 64, which * D + (h + 1) * 64)
+            ref = vqo.layernorm_quantize(b[None, sl], ln["gamma"][sl], ln["beta"][sl], ln["eps"], step, bits)["q"]
+            assert (qkv[which][:, h] == ref[0]).all(), (which, h)
