@@ -119,16 +119,23 @@ def _check(status, where):
         raise VitqError(status, where)
 
 
+# The handle of the current device's current stream without the Python stream object: 0.2 us against 2.8, in calls
+# whose launch takes 3 (197 x 384 quantized and through a linear: 16.3 us a pass, 10.9 so).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+        return _raw_stream(_current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return C.c_void_p(t)
-    return C.c_void_p(t.data_ptr())
+    """Address for a void pointer argument: of a tensor, or an integer as it is."""
+    if t is None or isinstance(t, int):
+        return t
+    return t.data_ptr()
 
 
 def row_stride_for(cols, storage_bits):
@@ -159,11 +166,8 @@ class QMat:
         return QMat(torch.zeros((rows, stride), dtype=torch.uint8, device=device), cols, bits, sb, unsigned)
 
     def c(self):
-        m = vq_qmat()
-        m.data = self.data.data_ptr() if self.data.numel() else None
-        m.bits, m.storage_bits, m.is_unsigned = self.bits, self.storage_bits, int(self.unsigned)
-        m.rows, m.cols, m.row_stride = self.rows, self.cols, self.row_stride
-        return m
+        return vq_qmat(self.data.data_ptr() if self.data.numel() else None, self.bits, self.storage_bits,
+                       int(self.unsigned), 0, self.rows, self.cols, self.row_stride)
 
 
 def _q(m):

@@ -53,3 +53,14 @@ def test_captured_step_replays_match_eager_and_oracle(name):
         torch.cuda.synchronize()
         got = y.cpu().numpy()
         assert np.array_equal(got, eager), "%s: replay %d differs from the eager result" % (name, rep)
+
+
+def test_calls_go_to_the_current_stream():
+    """The handle that the binding passes is that of torch's current stream, whichever that is."""
+    assert vitq._stream() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert vitq._stream() == side.cuda_stream != 0
+        with torch.cuda.stream(torch.cuda.default_stream()):
+            assert vitq._stream() == torch.cuda.default_stream().cuda_stream
+    assert vitq._stream() == torch.cuda.current_stream().cuda_stream
