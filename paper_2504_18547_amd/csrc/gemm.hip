@@ -552,17 +552,26 @@ __device__ __forceinline__ void epilogue_headnorm(const GemmParams &p, v16i (&ac
 // ---- integer-only epilogue: equivalent bias + comparator references with the scales absorbed ----
 // (Eq. 2, second form; Sec. IV-B.)  level = qmin + #{t : acc + b_int[c] > T[c][t]}, T non-decreasing
 // in t, so the count is found by bisection: 4 integer comparisons for up to 15 references, 8 for up
-// to 255, no branch, no floating point.  The tile keeps rows of kAbsRow entries in LDS (INT32_MAX
-// -- never exceeded -- beyond the last reference): the references themselves when there are at
-// most 15 per channel, else every sixteenth one (T[15], T[31], ...), which settles the first four
-// strides; the last four then probe one 16-entry stretch of the caller's table in global memory.
+// to 255, no branch, no floating point.  The tile keeps rows of kAbsRow entries in LDS: the references
+// themselves when there are at most 15 per channel, else every sixteenth one (T[15], T[31], ...), which
+// settles the first four strides; the last four then probe one 16-entry stretch of the caller's table
+// in global memory.
+// acc + b_int may leave 32 bits (a near-dead channel's bias lies at the int32 limits), T - b_int too, but there
+// saturation changes no comparison: acc is at most 2^30 in size.  So the references are taken relative to
+// the bias, and a row in LDS holds them ready to be compared with the accumulator as it is (absorbed_reference).
 constexpr int kAbsRow = 17;
-// WIDE: acc + b_int may leave 32 bits (see the staging of the biases): sums and comparisons in 64 bits.
-template <bool TBL_LDS, bool WIDE>
+// |acc| <= 2^(WB-1) * 2^(AB-1) * K, K <= 65536: with the operand factor 2^shift at most 2^30 for every pair of
+// operands.  T - b, held to that range, compares like T - b itself; INT32_MAX is never exceeded.
+template <int WB, int AB>
+__device__ __forceinline__ int absorbed_reference(int T, int b) {
+    constexpr int shift = Shift<WB, AB>::value, most = 1 << (30 - shift);
+    static_assert(WB + AB - 2 + 16 <= 30 - shift, "accumulators");
+    return min(max(__builtin_elementwise_sub_sat(T, b), -most), most) * (1 << shift);
+}
+template <bool TBL_LDS>
 __device__ __forceinline__ void epilogue_absorbed(const GemmParams &p, const v16i &acc, int shift, uint8_t *dst,
                                                   const int *lds_tbl, const int *glb_tbl, int64_t glb_row, const int *bint) {
     if (!dst) return;
-    using sum_t = std::conditional_t<WIDE, int64_t, int>;
     const int nthr = p.ab_nthr;
     float lv[16];
 #pragma unroll
@@ -572,29 +581,22 @@ __device__ __forceinline__ void epilogue_absorbed(const GemmParams &p, const v16
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = 4 * q + i;
-            const sum_t a = (sum_t)(acc[r] >> shift) + (sum_t)bq[i];
             int pos = 0;                                // references known to be exceeded
             if constexpr (TBL_LDS) {
-                // (a missing reference is INT32_MAX "never exceeded": a 64-bit sum above it can only
-                // occur with every real reference exceeded too, and pos is capped at their number)
 #pragma unroll
-                for (int step = 8; step >= 1; step >>= 1) {
-                    const int t = pos + step - 1;
-                    pos += ((!WIDE || t < nthr) && a > (sum_t)lds_tbl[r * kAbsRow + t]) ? step : 0;
-                }
+                for (int step = 8; step >= 1; step >>= 1)
+                    pos += acc[r] > lds_tbl[r * kAbsRow + pos + step - 1] ? step : 0;
             } else {
                 // strides 128..16 probe T[16(i+1) - 1]: entry i of the LDS row; strides 8..1 finish
                 // inside one 16-entry stretch of the caller's table
 #pragma unroll
-                for (int step = 128; step >= 16; step >>= 1) {
-                    const int t = pos + step - 1;
-                    pos += ((!WIDE || t < nthr) && a > (sum_t)lds_tbl[r * kAbsRow + ((pos + step) >> 4) - 1]) ? step : 0;
-                }
+                for (int step = 128; step >= 16; step >>= 1)
+                    pos += acc[r] > lds_tbl[r * kAbsRow + ((pos + step) >> 4) - 1] ? step : 0;
 #pragma unroll
                 for (int step = 8; step >= 1; step >>= 1) {
                     const int t = pos + step - 1;
-                    const int v = glb_tbl[(int64_t)r * glb_row + min(t, nthr - 1)];
-                    pos += (a > (t >= nthr ? (sum_t)INT32_MAX : (sum_t)v) && (!WIDE || t < nthr)) ? step : 0;
+                    const int v = __builtin_elementwise_sub_sat(glb_tbl[(int64_t)r * glb_row + min(t, nthr - 1)], bq[i]);
+                    pos += (acc[r] >> shift) > (t >= nthr ? INT32_MAX : v) ? step : 0;
                 }
             }
             lv[r] = (float)pos;
@@ -610,7 +612,7 @@ __device__ __forceinline__ void epilogue_absorbed(const GemmParams &p, const v16
 // argument all but exact (checked and bounded where the biases are staged), so v lies above T[b-1] and not above T[b+1].
 // us, four dependent reads and the table in registers over the main loop / this: 12,608 x 768 -> 768 19.2 / 16.2 (12.6 for
 // the floating-point requantizer), 50,432 rows 48.1 / 42.9, 25,216 x 1024 -> 3072 105.6 / 93.9.
-// row: the tile's table from this lane's first channel on, entries (T - b_int) << shift; ca, cb: spacing^-1 * 2^-shift and
+// row: the tile's table from this lane's first channel on; ca, cb: spacing^-1 * 2^-shift and
 // (b_int - T[0]) / spacing + 1/2 of the lane's sixteen channels.
 __device__ __forceinline__ void epilogue_absorbed_even(const GemmParams &p, const v16i &acc, uint8_t *dst, const int *row,
                                                        const float *ca, const float *cb) {
@@ -848,16 +850,13 @@ void gemm_kernel(GemmParams p) {
     // folded in.  The fold is exact unless the result is subnormal; a flag then sends the whole
     // tile through the exact operation sequence.
     if constexpr (ABSORBED) {
-        // per channel: the equivalent bias.  |acc| stays below 2^23 (K <= 65536), so acc + b_int fits
-        // 32 bits unless a bias lies within 2^23 of the int32 limits (a near-dead channel): such a
-        // tile takes the 64-bit form of the comparisons.
+        // per channel: the equivalent bias
         if (tid == 0) s_fold_bad[0] = 0;
         __syncthreads();
         for (int c = tid; c < TC; c += NT) {
             const int ch = min(c0 + c, p.Nout - 1);
             const int b = p.ab_bint ? p.ab_bint[ch] : 0;
             reinterpret_cast<int *>(s_raw)[c] = b;
-            int flags = (b > INT32_MAX - (1 << 23) || b < INT32_MIN + (1 << 23)) ? 3 : 0;
             // Up to 15 references: are they evenly spaced, as epilogue_absorbed_even needs?  Relative to the bias they have
             // to stay within 22 bits with the operand factor in 32, the spacing to be 4 or more and each of them within
             // 3/8 of it.  (A sum below 2^24 is exact in fp32 and a larger one beyond every reference; the roundings
@@ -876,11 +875,10 @@ void gemm_kernel(GemmParams p) {
 #pragma unroll
                 for (int e = 1; e < 14; ++e)
                     ok = ok && (e >= nthr || fabsf(((float)((int64_t)ref[e] - b) - first) * inv - (float)e) <= 0.375f);
-                if (!ok) flags |= 2;
+                if (!ok) s_fold_bad[0] = 1;
                 s_scs[c] = inv * (1.0f / (1 << Shift<WB, AB>::value));
                 s_bs[c] = fmaf(-first, inv, 0.5f);
             }
-            if (flags) atomicOr(s_fold_bad, flags);
         }
     } else if constexpr (EPI != kEpiGeneric) {
         if (tid == 0) s_fold_bad[0] = 0;
@@ -1226,8 +1224,7 @@ void gemm_kernel(GemmParams p) {
             // The pipeline buffers are free now: the tile's LDS table (see epilogue_absorbed) goes there.
             const int nthr = p.ab_nthr;
             constexpr bool in_lds = (EPI == kEpiAbsorbed);
-            const bool wide = (s_fold_bad[0] & 1) != 0;    // (written before the main loop)
-            const bool even = in_lds && s_fold_bad[0] == 0;
+            const bool even = in_lds && s_fold_bad[0] == 0;           // (written before the main loop)
             int *s_tbl = reinterpret_cast<int *>(smem);
             static_assert(TC * kAbsRow * 4 <= S * STAGE, "reference table exceeds the pipeline buffers");
 #pragma unroll
@@ -1236,8 +1233,7 @@ void gemm_kernel(GemmParams p) {
                 const int e = i % kAbsRow;
                 const int t = in_lds ? e : 16 * (e + 1) - 1;
                 if (i >= TC * kAbsRow) continue;
-                if (even) s_tbl[i] = (abs_ref[k] - reinterpret_cast<const int *>(s_raw)[i / kAbsRow]) * (1 << shift);
-                else s_tbl[i] = t >= nthr ? INT32_MAX : abs_ref[k];
+                s_tbl[i] = t >= nthr ? INT32_MAX : absorbed_reference<WB, AB>(abs_ref[k], reinterpret_cast<const int *>(s_raw)[i / kAbsRow]);
             }
             __syncthreads();
             int64_t tok_part[NTK];
@@ -1257,12 +1253,9 @@ void gemm_kernel(GemmParams p) {
                         store_zero_group(p, dst);
                     else if (even)
                         epilogue_absorbed_even(p, acc[ci][ti], dst, s_tbl + cl * kAbsRow, s_scs + cl, s_bs + cl);
-                    else if (wide)
-                        epilogue_absorbed<in_lds, true>(p, acc[ci][ti], shift, dst, s_tbl + cl * kAbsRow,
-                                                        p.ab_thr + (int64_t)min(cb, p.Nout - 16) * nthr, nthr, bint);
                     else
-                        epilogue_absorbed<in_lds, false>(p, acc[ci][ti], shift, dst, s_tbl + cl * kAbsRow,
-                                                         p.ab_thr + (int64_t)min(cb, p.Nout - 16) * nthr, nthr, bint);
+                        epilogue_absorbed<in_lds>(p, acc[ci][ti], shift, dst, s_tbl + cl * kAbsRow,
+                                                  p.ab_thr + (int64_t)min(cb, p.Nout - 16) * nthr, nthr, bint);
                 });
             });
             return;

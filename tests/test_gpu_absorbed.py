@@ -154,6 +154,35 @@ def test_equivalent_bias_at_the_int32_limits():
     _run(xq, wq, b_int, thr8, 4, 4, 8, sum_may_leave_int32=True)
 
 
+@pytest.mark.parametrize("bits_w,bits_a,bits_y,K", [
+    (8, 8, 4, 1024), (8, 8, 8, 1024), (8, 8, 4, 65536), (8, 8, 8, 65536), (4, 4, 4, 65536), (4, 4, 8, 65536), (2, 4, 4, 65536)])
+def test_largest_accumulators_with_biases_near_the_int32_limits(bits_w, bits_a, bits_y, K):
+    """Accumulators of both signs up to the largest that the operands allow (2^30 with 8-bit pairs of 65,536 values), beside
+    biases at distances from the limits from which the sum leaves 32 bits or just does not."""
+    M, Nout = 40, 80
+    lo_a, hi_a = vqo.qrange(bits_a)
+    lo_w, hi_w = vqo.qrange(bits_w)
+    rng = np.random.default_rng(K + bits_w + bits_y)
+    xq = rng.integers(lo_a, hi_a + 1, size=(M, K)).astype(np.int8)
+    wq = rng.integers(lo_w, hi_w + 1, size=(Nout, K)).astype(np.int8)
+    xq[0], xq[1], xq[2, : K // 2], xq[33] = lo_a, hi_a, lo_a, lo_a
+    wq[::2] = lo_w
+    wq[1::4] = hi_w
+    imax, imin = 2 ** 31 - 1, -2 ** 31
+    n = (1 << bits_y) - 1
+    for near in (1, 2 ** 20, 2 ** 22, 3 * 2 ** 22, 2 ** 24, 3 * 2 ** 28, 2 ** 30):     # (one distance for all channels of a tile)
+        off = rng.integers(near - 1, near + 2, Nout)
+        b_int = np.where(np.arange(Nout) & 2, imax - off, imin + off).astype(np.int32)
+        thr = np.sort(rng.integers(-3000, 3000, size=(Nout, n)), axis=1).astype(np.int32)
+        at_limit = np.clip(b_int[:, None].astype(np.int64) + np.sort(rng.integers(-2 ** 30, 2 ** 30, (Nout, n)), axis=1), imin, imax)
+        thr[6::3] = at_limit[6::3]
+        thr[7], thr[8] = imax, imin
+        ref = _run(xq, wq, b_int, thr, bits_w, bits_a, bits_y, sum_may_leave_int32=True)
+        assert (ref["overflow"] > 0) == (near <= K << (bits_w + bits_a - 2)) and set(vqo.qrange(bits_y)) <= set(np.unique(ref["yq"]))
+        spaced = np.clip(b_int.astype(np.int64), imin + 2 ** 20, imax - 2 ** 20)[:, None] + 16 * (np.arange(n) - n // 2)
+        _run(xq, wq, b_int, spaced.astype(np.int32), bits_w, bits_a, bits_y, sum_may_leave_int32=True)
+
+
 def test_argument_errors():
     xq, wq, s_w, bias = _operands(3, 8, 64, 24, 4, 4)       # 24 output channels: not a multiple of 16
     b_int, thr = vitq.vq_absorb_thresholds(0.05, s_w, bias, [0.1], 4)
