@@ -609,7 +609,7 @@ __device__ __forceinline__ void epilogue_absorbed(const GemmParams &p, const v16
 // The same count where every channel of the tile has nearly evenly spaced references, as absorbed scales give: with the
 // reference nearest to the sum, b = rint((v - T[0]) / spacing) kept inside the table, the count is b + (v > T[b]), one LDS
 // read per element instead of four dependent ones.  T[t] is within 3/8 of a spacing of T[0] + t * spacing and b's
-// argument all but exact (checked and bounded where the biases are staged), so v lies above T[b-1] and not above T[b+1].
+// argument right within 1/8 (checked and bounded where the biases are staged), so v lies above T[b-1] and not above T[b+1].
 // us, four dependent reads and the table in registers over the main loop / this: 12,608 x 768 -> 768 19.2 / 16.2 (12.6 for
 // the floating-point requantizer), 50,432 rows 48.1 / 42.9, 25,216 x 1024 -> 3072 105.6 / 93.9.
 // row: the tile's table from this lane's first channel on; ca, cb: spacing^-1 * 2^-shift and
@@ -859,8 +859,11 @@ void gemm_kernel(GemmParams p) {
             reinterpret_cast<int *>(s_raw)[c] = b;
             // Up to 15 references: are they evenly spaced, as epilogue_absorbed_even needs?  Relative to the bias they have
             // to stay within 22 bits with the operand factor in 32, the spacing to be 4 or more and each of them within
-            // 3/8 of it.  (A sum below 2^24 is exact in fp32 and a larger one beyond every reference; the roundings
-            // of the first reference, the spacing and the quotient move it by less than 2^-16.)
+            // 3/8 of it.  (A sum below 2^24 is exact in fp32 and a larger one beyond every reference.  A sum's place, in
+            // spacings from the first reference, has to be right within 1/2 - 3/8 = 1/8.  Its offset -T[0] / spacing is at most
+            // 2^22 / 4 in size, so rounding it moves the place by up to 2^-4 [2^-5 below 2^20]; the roundings of
+            // the spacing's reciprocal and of the quotient add less than 2^-16.  A closer spacing or a farther reach
+            // needs that 2^-4 counted again.)
             if constexpr (EPI == kEpiAbsorbed) {
                 const int nthr = p.ab_nthr;
                 const int *row = p.ab_thr + (int64_t)ch * nthr;

@@ -125,6 +125,39 @@ def test_evenly_spaced_references_and_where_that_ends(bits_w, bits_a, bits_y, M,
         _run(xq, wq, b_int, some, bits_w, bits_a, bits_y)
 
 
+@pytest.mark.parametrize("bits_w,bits_a,bits_y,K,sign", [(8, 8, 4, 1024, -1), (8, 8, 4, 1024, 1), (8, 8, 3, 1024, -1), (4, 4, 4, 65536, -1),
+                                                         (2, 4, 4, 65536, 1), (2, 4, 3, 65536, -1)])
+def test_narrowest_even_references_far_from_the_bias(bits_w, bits_a, bits_y, K, sign):
+    """Where the rounding of the nearest reference's index is largest: spacings from 4 on that are no dyadic numbers, references as
+    far off their places as still counts as even, as far from the bias as they may be, a sum at every integer between them."""
+    n, tail, M, Nout = (1 << bits_y) - 1, 9, 128, 128
+    reach = 2 ** 20 if bits_w == 2 else 2 ** 22
+    lo_a, hi_a = vqo.qrange(bits_a)
+    lo_w, _ = vqo.qrange(bits_w)
+    rng = np.random.default_rng(K + bits_w + bits_y)
+    x = np.zeros((M, K), np.int64)
+    x[:, :tail] = np.arange(-M // 2, M // 2)[:, None] // tail                # consecutive sums from token to token
+    x[:, :tail] += np.arange(tail)[None, :] < (np.arange(-M // 2, M // 2) % tail)[:, None]
+    w = np.full((Nout, K), lo_w)
+    w[:, :tail] = 1
+    full = min((reach - 512) // (-lo_w * max(-lo_a, hi_a)), K - tail - 1)
+    x[:, tail:tail + full] = lo_a if sign > 0 else hi_a
+    sums = x[:, :tail].sum(1) + lo_w * int(x[0, tail:].sum())
+    assert np.array_equal(np.diff(sums), np.ones(M - 1)) and abs(sums).max() < reach and abs(sums).min() > 0.7 * reach
+    b_int = rng.integers(-900, 900, Nout)
+    thr = np.empty((Nout, n), np.int64)
+    for c in range(Nout):
+        width = int(rng.integers(4 * (n - 1), 4 * (n - 1) + 4))
+        at = np.arange(n) * width / (n - 1)
+        off = rng.choice([-0.375, 0.375, 0.0], n) * width / (n - 1)
+        ref = np.where(off < 0, np.ceil(at + off), np.floor(at + off))
+        ref[0], ref[-1] = 0, width
+        assert (abs(ref - at) <= 0.375 * width / (n - 1)).all() and (np.diff(ref) >= 0).all()
+        thr[c] = sums[0] + int(rng.integers(2, M - 2 - width)) + ref + b_int[c]
+    ref = _run(x.astype(np.int8), w.astype(np.int8), b_int.astype(np.int32), thr.astype(np.int32), bits_w, bits_a, bits_y)
+    assert len(np.unique(ref["yq"])) == n + 1
+
+
 def test_equivalent_bias_at_the_int32_limits():
     """b_int is clamped to int32 by the preparation step, so a near-dead channel carries INT32_MAX or
     INT32_MIN; the sum with an accumulator of the same sign then leaves 32 bits, and the oracle
