@@ -610,8 +610,8 @@ __device__ __forceinline__ void epilogue_absorbed(const GemmParams &p, const v16
 // reference nearest to the sum, b = rint((v - T[0]) / spacing) kept inside the table, the count is b + (v > T[b]), one LDS
 // read per element instead of four dependent ones.  T[t] is within 3/8 of a spacing of T[0] + t * spacing and b's
 // argument right within 1/8 (checked and bounded where the biases are staged), so v lies above T[b-1] and not above T[b+1].
-// us, four dependent reads and the table in registers over the main loop / this: 12,608 x 768 -> 768 19.2 / 16.2 (12.6 for
-// the floating-point requantizer), 50,432 rows 48.1 / 42.9, 25,216 x 1024 -> 3072 105.6 / 93.9.
+// us, four dependent reads / this: 12,608 x 768 -> 768 17.4 / 15.0 (12.6 for the floating-point requantizer), 50,432 rows
+// 45.6 / 39.0, 25,216 x 1024 -> 3072 100 / 90.
 // row: the tile's table from this lane's first channel on; ca, cb: spacing^-1 * 2^-shift and
 // (b_int - T[0]) / spacing + 1/2 of the lane's sixteen channels.
 __device__ __forceinline__ void epilogue_absorbed_even(const GemmParams &p, const v16i &acc, uint8_t *dst, const int *row,
@@ -825,22 +825,24 @@ void gemm_kernel(GemmParams p) {
     };
     // Integer-only epilogue: this lane's share of the tile's comparator references, requested when the last operand
     // load has retired (no hand-counted wait follows), so that it arrives behind the last k-stage.  Requested ahead of
-    // the operands it was spilled over the main loop: 12,608 x 768 -> 768 18.8 us, 16.2 without any table.
-    constexpr int ABS_ITERS = ABSORBED ? (TC * kAbsRow + NT - 1) / NT : 1;
+    // the operands it was spilled over the main loop: 12,608 x 768 -> 768 18.8 us, 16.2 without any table.  8-bit operands leave
+    // registers for it, and their last k-stage is too short to hide it: there it goes ahead (12,608 rows 19.3 / 18.9).
+    constexpr int ABS_ITERS = ABSORBED ? TC * 16 / NT : 1;               // sixteen entries per channel (kAbsRow spreads the banks)
+    static_assert(!ABSORBED || TC * 16 % NT == 0, "whole rounds");
     [[maybe_unused]] int abs_ref[ABS_ITERS];
     [[maybe_unused]] auto load_references = [&] {
         if constexpr (ABSORBED) {
             const int nthr = p.ab_nthr;
 #pragma unroll
             for (int k = 0; k < ABS_ITERS; ++k) {
-                const int i = min(k * NT + tid, TC * kAbsRow - 1);
-                const int c = i / kAbsRow, e = i - kAbsRow * c;              // entry e of channel c
-                const int t = (EPI == kEpiAbsorbed) ? e : 16 * (e + 1) - 1;  // the reference it holds
+                const int i = k * NT + tid, c = i >> 4, e = i & 15;          // entry e of channel c
+                const int t = (EPI == kEpiAbsorbed) ? e : 16 * e + 15;       // the reference it holds
                 const int ch = min(c0 + c, p.Nout - 1);
                 abs_ref[k] = p.ab_thr[(int64_t)ch * nthr + min(t, nthr - 1)];           // (pads: replaced when stored)
             }
         }
     };
+    if constexpr (WB == 8 && AB == 8) load_references();
 #pragma unroll
     for (int st = 0; st < S - 1; ++st)
         if (st < nk) issue(st);
@@ -852,37 +854,7 @@ void gemm_kernel(GemmParams p) {
     if constexpr (ABSORBED) {
         // per channel: the equivalent bias
         if (tid == 0) s_fold_bad[0] = 0;
-        __syncthreads();
-        for (int c = tid; c < TC; c += NT) {
-            const int ch = min(c0 + c, p.Nout - 1);
-            const int b = p.ab_bint ? p.ab_bint[ch] : 0;
-            reinterpret_cast<int *>(s_raw)[c] = b;
-            // Up to 15 references: are they evenly spaced, as epilogue_absorbed_even needs?  Relative to the bias they have
-            // to stay within 22 bits with the operand factor in 32, the spacing to be 4 or more and each of them within
-            // 3/8 of it.  (A sum below 2^24 is exact in fp32 and a larger one beyond every reference.  A sum's place, in
-            // spacings from the first reference, has to be right within 1/2 - 3/8 = 1/8.  Its offset -T[0] / spacing is at most
-            // 2^22 / 4 in size, so rounding it moves the place by up to 2^-4 [2^-5 below 2^20]; the roundings of
-            // the spacing's reciprocal and of the quotient add less than 2^-16.  A closer spacing or a farther reach
-            // needs that 2^-4 counted again.)
-            if constexpr (EPI == kEpiAbsorbed) {
-                const int nthr = p.ab_nthr;
-                const int *row = p.ab_thr + (int64_t)ch * nthr;
-                int ref[15];
-#pragma unroll
-                for (int e = 0; e < 15; ++e) ref[e] = row[min(e, nthr - 1)];
-                const int64_t low = (int64_t)ref[0] - b, high = (int64_t)ref[14] - b;       // (they do not decrease)
-                const float first = (float)low;
-                const float gap = (float)(high - low) / (float)(nthr - 1), inv = 1.0f / gap;
-                constexpr int reach = 1 << (Shift<WB, AB>::value > 8 ? 20 : 22);
-                bool ok = low >= -reach && high < reach && gap >= 4.0f;                     // (one reference: not a number)
-#pragma unroll
-                for (int e = 1; e < 14; ++e)
-                    ok = ok && (e >= nthr || fabsf(((float)((int64_t)ref[e] - b) - first) * inv - (float)e) <= 0.375f);
-                if (!ok) s_fold_bad[0] = 1;
-                s_scs[c] = inv * (1.0f / (1 << Shift<WB, AB>::value));
-                s_bs[c] = fmaf(-first, inv, 0.5f);
-            }
-        }
+        for (int c = tid; c < TC; c += NT) reinterpret_cast<int *>(s_raw)[c] = p.ab_bint ? p.ab_bint[min(c0 + c, p.Nout - 1)] : 0;
     } else if constexpr (EPI != kEpiGeneric) {
         if (tid == 0) s_fold_bad[0] = 0;
         __syncthreads();
@@ -1151,7 +1123,6 @@ void gemm_kernel(GemmParams p) {
         sync_stage(0);
         read_step(0, I0{}, I0{});
         for (int kt = 0; kt < nk - 1; ++kt) steps(kt, std::true_type{});
-        load_references();
         steps(nk - 1, std::false_type{});
     }
     __syncthreads();
@@ -1227,18 +1198,53 @@ void gemm_kernel(GemmParams p) {
             // The pipeline buffers are free now: the tile's LDS table (see epilogue_absorbed) goes there.
             const int nthr = p.ab_nthr;
             constexpr bool in_lds = (EPI == kEpiAbsorbed);
-            const bool even = in_lds && s_fold_bad[0] == 0;           // (written before the main loop)
             int *s_tbl = reinterpret_cast<int *>(smem);
             static_assert(TC * kAbsRow * 4 <= S * STAGE, "reference table exceeds the pipeline buffers");
 #pragma unroll
             for (int k = 0; k < ABS_ITERS; ++k) {
-                const int i = k * NT + tid;
-                const int e = i % kAbsRow;
-                const int t = in_lds ? e : 16 * (e + 1) - 1;
-                if (i >= TC * kAbsRow) continue;
-                s_tbl[i] = t >= nthr ? INT32_MAX : absorbed_reference<WB, AB>(abs_ref[k], reinterpret_cast<const int *>(s_raw)[i / kAbsRow]);
+                const int i = k * NT + tid, c = i >> 4, e = i & 15;
+                const int t = in_lds ? e : 16 * e + 15;
+                s_tbl[c * kAbsRow + e] = t >= nthr ? INT32_MAX : absorbed_reference<WB, AB>(abs_ref[k], reinterpret_cast<const int *>(s_raw)[c]);
             }
             __syncthreads();
+            if constexpr (in_lds) {
+                // Are they evenly spaced, as epilogue_absorbed_even needs?  Relative to the bias they have to stay within 22 bits
+                // (20 with an operand factor above 2^8), the spacing to be 4 or more and each of them within 3/8
+                // of it.  (A sum below 2^24 is exact in fp32 and a larger one beyond every reference.  A sum's place, in
+                // spacings from the first reference, has to be right within 1/2 - 3/8 = 1/8.  Its offset -T[0] / spacing is at
+                // most 2^22 / 4 in size, so rounding it moves the place by up to 2^-4 [2^-5 below 2^20]; the roundings of
+                // the spacing's reciprocal and of the quotient add less than 2^-16.  A closer spacing or a farther reach
+                // needs that 2^-4 counted again.)
+                // Four neighbouring lanes look at a channel's row here, where it is in LDS.  One lane per channel, reading the caller's
+                // table ahead of the main loop, held every tile up, and one that is not even had nothing for it.  12,608 x 768 ->
+                // 768, us, no look / that one / this one: references at random 19.1 / 21.1 / 17.4, even ones - / 16.4 / 15.0;
+                // 197 rows 12.6 / 14.6 / 11.1 and - / 10.7 / 9.2; 8-bit operands 20.2 / 22.9 / 20.4 and - / 19.5 / 18.1.
+                static_assert(4 * TC % NT == 0, "whole groups of four lanes");
+                constexpr int reach = 1 << (shift > 8 ? 20 : 22);
+#pragma unroll
+                for (int it = 0; it < 4 * TC / NT; ++it) {
+                    const int c = (it * NT + tid) >> 2;
+                    const int at = min(4 * (tid & 3), max(nthr - 4, 0));           // this lane's four (the last ones overlap)
+                    int ref[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ref[e] = s_tbl[c * kAbsRow + min(at + e, nthr - 1)];
+                    const int low = __builtin_amdgcn_mov_dpp(ref[0], 0x00, 0xF, 0xF, true);      // of the group's first lane
+                    const int high = __builtin_amdgcn_mov_dpp(ref[3], 0xFF, 0xF, 0xF, true);     // and its last
+                    const int width = (int)((u32)high - (u32)low);       // (wraps only where low or high are out of reach)
+                    const float inv = (float)(nthr - 1) * __builtin_amdgcn_rcpf((float)width);
+                    bool ok = low > -(reach << shift) && high < (reach << shift) && width >= ((4 * (nthr - 1)) << shift);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)                                    // (one reference: not a number)
+                        ok = ok & (fabsf((float)(int)((u32)ref[e] - (u32)low) * inv - (float)min(at + e, nthr - 1)) <= 0.375f);
+                    if (!ok) s_fold_bad[0] = 1;
+                    if ((tid & 3) == 0) {
+                        s_scs[c] = inv;
+                        s_bs[c] = fmaf(-(float)low, inv, 0.5f);
+                    }
+                }
+                __syncthreads();
+            }
+            const bool even = in_lds && s_fold_bad[0] == 0;
             int64_t tok_part[NTK];
 #pragma unroll
             for (int ti = 0; ti < NTK; ++ti) tok_part[ti] = packed_token_part(p, t0 + wave_t * WT + ti * 32 + li);

@@ -125,6 +125,25 @@ def test_evenly_spaced_references_and_where_that_ends(bits_w, bits_a, bits_y, M,
         _run(xq, wq, b_int, some, bits_w, bits_a, bits_y)
 
 
+@pytest.mark.parametrize("bits_w,bits_a,bits_y", [(4, 4, 4), (8, 8, 4), (2, 4, 4), (4, 4, 3), (4, 4, 2)])
+def test_one_reference_off_its_place_is_seen_wherever_it_is(bits_w, bits_a, bits_y):
+    """Evenly spaced tables but for one reference, at every place of the row and in channels all over the tile: nearer to a
+    neighbour's place than to its own, so that a count taken from the even spacing would be wrong for sums beside it."""
+    M, K, Nout = 200, 160, 144
+    xq, wq, _, _ = _operands(77 + bits_y, M, K, Nout, bits_w, bits_a)
+    n = (1 << bits_y) - 1
+    b_int = np.random.default_rng(78).integers(-50, 50, Nout).astype(np.int32)
+    std = float(np.std(xq.astype(np.int64) @ wq.astype(np.int64).T))
+    gap = max(16, int(2.5 * std) * 2 // n)
+    even = np.tile(((np.arange(n) - n // 2) * gap).astype(np.int32), (Nout, 1))
+    _run(xq, wq, b_int, even, bits_w, bits_a, bits_y, want_acc=False)
+    for at in range(n):
+        for side in (-1, 1):
+            thr = even.copy()
+            thr[(37 * at + (64 if side > 0 else 0)) % Nout, at] += side * (gap * 3 // 4)
+            _run(xq, wq, b_int, thr, bits_w, bits_a, bits_y, want_acc=False)
+
+
 @pytest.mark.parametrize("bits_w,bits_a,bits_y,K,sign", [(8, 8, 4, 1024, -1), (8, 8, 4, 1024, 1), (8, 8, 3, 1024, -1), (4, 4, 4, 65536, -1),
                                                          (2, 4, 4, 65536, 1), (2, 4, 3, 65536, -1)])
 def test_narrowest_even_references_far_from_the_bias(bits_w, bits_a, bits_y, K, sign):
