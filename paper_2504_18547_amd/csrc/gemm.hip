@@ -1566,33 +1566,17 @@ bool use_split(const GemmParams &p, int wb, int ab, int epi) {
 // Large fp32 results of a long contraction are bound by their stores, and a deal that saves less than a
 // sixteenth does not make up for twice the tiles: 28,368 x 1024 -> 3072 113 us on large tiles, 121 on small
 // ones, 44,128 rows 181 and 190 (4096 channels: within 2 % either way).
-// The integer-only epilogue has less room for its references on the smaller tile (four waves stage what
-// eight do: 9 spilled registers against 5), so an even deal of any size keeps the larger one (6,304 x 768 ->
-// 768: 16.2 us against 16.9).  With more than 15 references per channel (49 spilled against 23) the smaller
-// tile is 1.1 to 1.24 times ahead where every CU has one at most, but not
-//   - up to 160 rows, where the second half of a large tile is empty anyway (128 x 384 -> 384 with 255
-//     references 25.0 us on 128x256, 26.5 on 128x128; from K 2048 on it is ahead there too, by 2 %),
-//   - where the references and weights of an XCD's share of the tiles crowd its 4 MB L2 (each small tile
-//     reads them for half as many rows; a weight byte counts one and a half): 255 references, K 1024, 1,536
-//     channels 1.17 times ahead, 2,016 0.97; K 384, 2,016 channels 1.18, 2,688 0.96; 31 references, K 1024,
-//     3,072 channels 1.06, 3,584 0.93 (a long walk of K hides a little more: K 3072, 255 references, 1,152
-//     channels 1.01 to 1.14, 1,344 0.97),
-//   - up to 64 channels of a short contraction (15 references too: 126 x 115 -> 32 6.3 us against 6.6);
-// and of the larger grids three small tiles against two large ones pay with 255 references only (12,608 x
-// 768 -> 768 64.1 us on large tiles, 61.4 on small; with 63 and 31 references 0.93 to 0.98 of the speed).
+// The integer-only epilogues gain less from more workgroups beside each other: on an even deal they keep the larger tile (us, large
+// / small: 6,304 x 768 -> 768 with 15 references 11.15 / 11.42, 50,432 rows 39.0 / 41.3; with 255 145 / 149) and take the
+// smaller one on any other (12,608 x 768 -> 768 with 15 16.6 / 14.7, with 31 44.5 / 36.1, with 255 61.5 / 48.8; 513 x 1024 ->
+// 3584 28.6 / 21.2 and 35.6 / 24.9; 25,216 x 1024 -> 3072, 20 units to 19, with 63 217 / 205).  With more than 127
+// references, a cache line for each probe, 20 to 19 is too little (304 / 311; 6,304 x 768 -> 3072, 6 to 5, 91.2 / 85.3).
 bool small_tile(const GemmParams &p, int epi) {
     constexpr int64_t kCUs = 256;
     const int64_t n_ct = (p.Nout + 127) / 128;
     const int64_t small = n_ct * (((int64_t)p.M + 127) / 128), large = n_ct * (((int64_t)p.M + 255) / 256);
     const int64_t cs = (small + kCUs - 1) / kCUs, cl = 2 * ((large + kCUs - 1) / kCUs);   // 128x128 units of the busiest CU
-    if ((epi == kEpiAbsorbed || epi == kEpiAbsorbedBig) && p.Nout <= 64 && p.K < 384) return false;
-    if (epi == kEpiAbsorbedBig) {
-        if (cs > 1) return 4 * cs <= 3 * cl && p.ab_nthr > 127;
-        const int64_t channels = small * (128 / 8) < p.Nout ? small * (128 / 8) : p.Nout;     // of an XCD's tiles
-        const bool long_k = p.K >= 2048;
-        return (p.M > 160 || long_k) && channels * (4 * p.ab_nthr + 3 * p.K / 4) <= (long_k ? 4000000 : 3000000);
-    }
-    if (epi == kEpiAbsorbed) return cs < cl;
+    if (epi == kEpiAbsorbed || epi == kEpiAbsorbedBig) return p.ab_nthr > 127 ? 16 * cs <= 15 * cl : cs < cl;
     if (epi == kEpiGeneric && p.M > 128 && p.M <= 160) return false;
     if (epi == kEpiF32 && p.K >= 1024 && cl > 16) return false;
     return epi == kEpiQuantGelu || cs < cl || cs <= 2;

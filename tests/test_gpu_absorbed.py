@@ -58,9 +58,9 @@ def _run(xq, wq, b_int, thr, bits_w, bits_a, bits_y, want_acc=True, sum_may_leav
     (4, 4, 4, 2177, 600, 2048),     # 288 small tiles, 144 large: an even deal, 128x256, five k-stages and a tail
     (4, 4, 8, 2177, 600, 2048),     # the same with 255 references
     (4, 4, 8, 4249, 72, 2064),      # 255 references, 578 small tiles, 289 large: three units against four, 128x128
-    (4, 4, 6, 4249, 72, 2064),      # the same with 63 references: 128x256
+    (4, 4, 6, 4249, 72, 2064),      # the same with 63 references
     (4, 4, 8, 200, 400, 48),        # one small tile per CU, 128x128
-    (4, 4, 8, 513, 96, 4096),       # 160 of them, whose references crowd an L2: 128x256
+    (4, 4, 8, 513, 96, 4096),       # 160 of them
 ])
 def test_against_oracle(bits_w, bits_a, bits_y, M, K, Nout):
     xq, wq, s_w, bias = _operands(1000 + M + bits_y, M, K, Nout, bits_w, bits_a)
