@@ -390,8 +390,7 @@ __device__ __forceinline__ void epilogue_quant(const GemmParams &p, const v16i &
 // gamma / beta / the folded scales are wave-uniform: staged in LDS once per tile and read as
 // broadcasts.  tmp: this lane's column of 32 x 64 floats in LDS.
 // Bound by VALU issue at two waves per SIMD.  9,900 tokens x 384 -> 1152, 2-bit weights: 28.7 us with a division per element
-// and a verification branch per level, 22.9 with the quotients below and one test per eight levels (though the
-// rare paths' control flow makes the compiler spill part of the other token blocks' accumulators).
+// and a verification branch per level, 22.9 with the quotients below and one test per eight levels.
 constexpr float kHnGuard = 0x1p-21f;   // unit of the guard that lets a guessed level stand (see the LayerNorm kernel)
 template <int SB, int NTK, int PAIR>   // PAIR: token blocks 2*PAIR and 2*PAIR + 1 of the wave's NTK
 __device__ __forceinline__ void epilogue_headnorm(const GemmParams &p, v16i (&acc)[2][NTK], int shift, uint8_t *dst,
@@ -432,6 +431,7 @@ __device__ __forceinline__ void epilogue_headnorm(const GemmParams &p, v16i (&ac
         const float pr = d1 * d2;
         m2 = m2 + pr;
     });
+    asm volatile("" : "+v"(m2));   // (or its chain sinks past the branch below, all deviations and means held until there)
     const bool walked = fabsf(mu) <= 3.0e38f && least >= 2u * __float_as_uint(0x1p-98f) - 1u;
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(!walked) != 0, 0)) {
         // (rare; from LDS and rolled up, so that its divisions cost the others no registers)
