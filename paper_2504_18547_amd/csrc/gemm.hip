@@ -388,9 +388,10 @@ __device__ __forceinline__ void epilogue_quant(const GemmParams &p, const v16i &
 // provably far from every boundary, and otherwise picks which two comparisons are evaluated.
 // The fp32 linear output never leaves registers.
 // gamma / beta / the folded scales are wave-uniform: staged in LDS once per tile and read as
-// broadcasts.  tmp: this lane's column of 32 x 64 floats in LDS.
-// Bound by VALU issue at two waves per SIMD.  9,900 tokens x 384 -> 1152, 2-bit weights: 28.7 us with a division per element
-// and a verification branch per level, 22.9 with the quotients below and one test per eight levels.
+// broadcasts.  tmp: this lane's column of 64 x 64 floats in LDS.
+// Bound by VALU issue at two waves per SIMD.  The attention block with it, us, with a division per element and a verification
+// branch per level / with the quotients below and one test per eight levels, the comparator in line / behind them: 256 ViT-B
+// images in 4 bits 328 / 276 / 273, in 8 bits 416 / 372 / 362; 50 DeiT-S images, 2-bit weights 54.1 / 45.5 / 44.9.
 constexpr float kHnGuard = 0x1p-21f;   // unit of the guard that lets a guessed level stand (see the LayerNorm kernel)
 template <int SB, int NTK, int PAIR>   // PAIR: token blocks 2*PAIR and 2*PAIR + 1 of the wave's NTK
 __device__ __forceinline__ void epilogue_headnorm(const GemmParams &p, v16i (&acc)[2][NTK], int shift, uint8_t *dst,
@@ -437,20 +438,17 @@ __device__ __forceinline__ void epilogue_headnorm(const GemmParams &p, v16i (&ac
         // (rare; from LDS and rolled up, so that its divisions cost the others no registers)
         mu = 0.0f;
         m2 = 0.0f;
-        static_for<2>([&](auto H) {
-            constexpr int h = decltype(H)::value;
 #pragma unroll
-            for (int i = 0; i < 32; ++i) tmp[64 * i] = v[32 * h + i];
+        for (int i = 0; i < 64; ++i) tmp[64 * i] = v[i];
 #pragma unroll 1
-            for (int i = 0; i < 32; ++i) {
-                const float x = tmp[64 * i];
-                const float d1 = x - mu;
-                mu = mu + d1 / (float)(32 * h + i + 1);
-                const float d2 = x - mu;
-                const float pr = d1 * d2;
-                m2 = m2 + pr;
-            }
-        });
+        for (int i = 0; i < 64; ++i) {
+            const float x = tmp[64 * i];
+            const float d1 = x - mu;
+            mu = mu + d1 / (float)(i + 1);
+            const float d2 = x - mu;
+            const float pr = d1 * d2;
+            m2 = m2 + pr;
+        }
     }
     const float nf = 64.0f;
     const float ne = nf * p.hn_eps;
@@ -469,6 +467,7 @@ __device__ __forceinline__ void epilogue_headnorm(const GemmParams &p, v16i (&ac
     // of theirs; the figures are compared as bit patterns, where a NaN is above everything and fails it.
     // Levels leave biased, 0 .. qmax - qmin, one byte each: w8[2*j], w8[2*j + 1] hold channels 8*j .. 8*j + 7.
     u32 w8[16];
+    u32 unsure = 0;                                          // groups of eight channels with one to be compared
     static_for<8>([&](auto J) {
         constexpr int j = decltype(J)::value;
         float lv[8];
@@ -485,32 +484,10 @@ __device__ __forceinline__ void epilogue_headnorm(const GemmParams &p, v16i (&ac
             lv[r] = __builtin_amdgcn_fmed3f(tt, qminf, qmaxf);
         }
         const float fig = __uint_as_float(worst) + fmaf(__uint_as_float(bmax), 3.0f * kHnGuard, 3.0f * kHnGuard);
-        const bool sure = stats_ok && fig <= 0.5f;
-        if (__builtin_amdgcn_ballot_w64(!sure) != 0) {
+        if (!(stats_ok && fig <= 0.5f)) {                    // (rare: decided below)
+            unsure |= 1u << j;
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const int i = 8 * j + r;
-                const float bt = bp[i];
-                const float a = v[i] - mu;
-                const float g = a * gp[i];
-                const float gs = g * fabsf(g);
-                const float L = gs * nf;
-                auto above = [&](float k) {
-                    const float rk = (k - 0.5f) * step;
-                    const float cc = rk - bt;
-                    const float cs = cc * fabsf(cc);
-                    const float R = cs * V;
-                    return L > R;
-                };
-                float c = (lv[r] == lv[r]) ? fminf(fmaxf(lv[r], qminf), qmaxf) : qminf;
-                for (int it = 0; it <= span; ++it) {
-                    const bool low_ok = (c <= qminf) || above(c);
-                    const bool high_ok = (c >= qmaxf) || !above(c + 1.0f);
-                    if (low_ok && high_ok) break;
-                    c = c + (!low_ok ? -1.0f : 1.0f);
-                }
-                lv[r] = c;
-            }
+            for (int r = 0; r < 8; ++r) tmp[64 * (8 * j + r)] = v[8 * j + r];
         }
         u32 ev = 0, od = 0;
 #pragma unroll
@@ -546,6 +523,51 @@ __device__ __forceinline__ void epilogue_headnorm(const GemmParams &p, v16i (&ac
             }
             *reinterpret_cast<uint4 *>(dst + 16 * q) = make_uint4(w[0], w[1], w[2], w[3]);
         }
+    }
+    // The comparator, for groups with a guess near a boundary: from LDS and over what was stored, when nothing else of this
+    // token is held.  (It is not that rare with 8-bit levels: a wave has such a lane in one of twelve groups or so.)
+    while (unsure) {
+        const int j = __builtin_ctz(unsure);
+        unsure &= unsure - 1;
+        float L[8], bt[8], lv[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int i = 8 * j + r;
+            bt[r] = bp[i];
+            const float a = tmp[64 * i] - mu;
+            const float g = a * gp[i];
+            const float gs = g * fabsf(g);
+            L[r] = gs * nf;
+            lv[r] = rintf(fmaf(g, rsr, bt[r] * rstep));
+            lv[r] = (lv[r] == lv[r]) ? fminf(fmaxf(lv[r], qminf), qmaxf) : qminf;
+        }
+        auto above = [&](int r, float k) {
+            const float rk = (k - 0.5f) * step;
+            const float cc = rk - bt[r];
+            const float cs = cc * fabsf(cc);
+            const float R = cs * V;
+            return L[r] > R;
+        };
+        for (int it = 0; it <= span; ++it) {
+            bool moved = false;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const bool low_ok = (lv[r] <= qminf) || above(r, lv[r]);
+                const bool high_ok = (lv[r] >= qmaxf) || !above(r, lv[r] + 1.0f);
+                const float d = !low_ok ? -1.0f : (!high_ok ? 1.0f : 0.0f);
+                lv[r] = lv[r] + d;
+                moved = moved || d != 0.0f;
+            }
+            if (!moved) break;
+        }
+        u32 w[2] = {0, 0};
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            if constexpr (SB == 4) w[0] |= ((u32)(int)lv[r] & 0xFu) << (4 * r);
+            else w[r / 4] |= ((u32)(int)lv[r] & 0xFFu) << (8 * (r % 4));
+        }
+        if constexpr (SB == 4) *reinterpret_cast<u32 *>(dst + 4 * j) = w[0];
+        else *reinterpret_cast<uint2 *>(dst + 8 * j) = make_uint2(w[0], w[1]);
     }
 }
 
@@ -708,6 +730,10 @@ __device__ __forceinline__ void pin_frags(v4i (&f)[N]) {
     for (int i = 0; i < N; ++i) asm volatile("" : "+v"(f[i]));
 }
 
+// LDS of the k-stages; the head-norm epilogue keeps 64 values per lane there afterwards
+template <int EPI, int WAVES, int STAGES>
+constexpr int pipeline_lds = EPI == kEpiHeadNorm && WAVES * 16384 > STAGES ? WAVES * 16384 : STAGES;
+
 template <int WB, int AB, int TC, int TT, int WAVES_C, int WAVES_T, int BK, int S, int OCC, int EPI>
 __global__ __launch_bounds__(WAVES_C *WAVES_T * 64, OCC)
 void gemm_kernel(GemmParams p) {
@@ -725,7 +751,7 @@ void gemm_kernel(GemmParams p) {
     constexpr bool ABSORBED = (EPI == kEpiAbsorbed || EPI == kEpiAbsorbedBig);   // integer-only epilogue
 
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    float *s_scs = reinterpret_cast<float *>(smem + S * STAGE);           // [TC] folded scales
+    float *s_scs = reinterpret_cast<float *>(smem + pipeline_lds<EPI, WAVES_C * WAVES_T, S * STAGE>);     // [TC] folded scales
     float *s_bs = s_scs + TC;                                             // [TC] biases
     int *s_fold_bad = reinterpret_cast<int *>(s_bs + TC);                 // [1] flag
     [[maybe_unused]] float *s_raw = s_bs + TC + 4;                        // [TC] plain scales (fp32, head-norm epilogues)
@@ -1179,8 +1205,7 @@ void gemm_kernel(GemmParams p) {
                 const float *sc64 = (fold_ok ? s_scs : s_raw) + wave_c * WC;
                 const int sh = fold_ok ? 0 : shift;
                 if constexpr (EPI == kEpiHeadNorm) {
-                    static_assert(WAVES_C * WAVES_T * 8192 <= S * STAGE, "the pipeline buffers hold what a wave walks again");
-                    float *tmp = reinterpret_cast<float *>(smem) + wave * 2048 + lane;
+                    float *tmp = reinterpret_cast<float *>(smem) + wave * 4096 + lane;
                     static_for<NTK / 2>([&](auto PI) {
                         constexpr int pair = decltype(PI)::value;
                         const int64_t tk = packed_token_part(p, t0 + wave_t * WT + 64 * pair + 32 * g + li);
@@ -1482,7 +1507,7 @@ hipError_t launch_split(const GemmParams &p, int epi, hipStream_t stream) {
 
 template <int WB, int AB, int TC, int TT, int WAVES_C, int WAVES_T, int BK, int S, int OCC, int EPI>
 hipError_t launch(const GemmParams &p, hipStream_t stream) {
-    constexpr size_t lds = S * ((size_t)TC * (BK * WB / 8) + (size_t)TT * (BK * AB / 8)) + 2 * TC * sizeof(float) + 16 +
+    constexpr size_t lds = pipeline_lds<EPI, WAVES_C * WAVES_T, S * (TC * (BK * WB / 8) + TT * (BK * AB / 8))> + 2 * TC * sizeof(float) + 16 +
                            ((EPI == kEpiHeadNorm || EPI == kEpiF32 || EPI == kEpiAbsorbed || EPI == kEpiAbsorbedBig) ? TC * sizeof(float) : 0) +
                            (EPI == kEpiHeadNorm ? 2 * TC * sizeof(float) : 0);
     auto kern = gemm_kernel<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, EPI>;

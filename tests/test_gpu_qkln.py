@@ -253,3 +253,39 @@ def test_fused_epilogue_tokens_whose_mean_needs_the_division(bits):
             sl = slice(which * D + h * 64, which * D + (h + 1) * 64)
             ref = vqo.layernorm_quantize(b[None, sl], ln["gamma"][sl], ln["beta"][sl], ln["eps"], step, bits)["q"]
             assert (qkv[which][:, h] == ref[0]).all(), (which, h)
+
+
+@pytest.mark.parametrize("bits_w,bits", [(4, 4), (2, 4), (3, 3), (8, 8)])
+def test_fused_epilogue_single_values_beside_a_boundary(bits_w, bits):
+    """Ordinary weights, so that every token differs, and in each channel one token's value beside a boundary of its level (the
+    others' are where they fall): groups of eight channels that go to the comparator in one lane and not in the next."""
+    dims = dict(D=256, H=4, N=45, hidden=0)
+    D, H, N, B = 256, 4, 45, 3
+    lo, hi = vqo.qrange(bits)
+    lo_w, hi_w = vqo.qrange(bits_w)
+    sa = storage_of(bits)
+    rng = np.random.default_rng(990 + bits_w + bits)
+    w = {"w_qkv": rng.integers(lo_w, hi_w + 1, (3 * D, D)).astype(np.int8), "sw_qkv": rng.uniform(0.005, 0.02, 3 * D).astype(np.float32),
+         "b_qkv": (rng.standard_normal(3 * D) * 0.2).astype(np.float32),
+         "w_proj": rng.integers(lo_w, hi_w + 1, (D, D)).astype(np.int8), "sw_proj": np.full(D, 0.01, np.float32), "b_proj": np.zeros(D, np.float32)}
+    x = rng.integers(lo, hi + 1, (B * N, D)).astype(np.int8)
+    steps = dict(s_x=np.float32(0.05), s_q=np.float32(2.5 / hi), s_k=np.float32(3.0 / hi), s_v=np.float32(3.0 / hi), s_o=0.1, scale=0.125)
+    y = vqo.linear(x, steps["s_x"], w["w_qkv"], w["sw_qkv"], bias=w["b_qkv"])["y"]
+    ln = _ln(D)
+    ln["gamma"][::7] *= -1
+    ln["beta"] = _planted_beta(y, ln["gamma"], ln["beta"], ln["eps"], (steps["s_q"], steps["s_k"]), bits, rng)
+    wd, gamma, beta = device_weights(w, bits_w), dev(ln["gamma"]), dev(ln["beta"])
+    dump = {"qkv": torch.zeros((3 * B * H * N, 64 * sa // 8), dtype=torch.uint8, device="cuda")}
+    desc = vitq.make_block_desc(dims, bits, bits, sa, wd, steps, dump, qkln=dict(gamma=gamma, beta=beta, eps=ln["eps"]))
+    ws = torch.empty(vitq.vq_attention_block_workspace(desc, B), dtype=torch.uint8, device="cuda")
+    out = torch.empty((B * N, D), dtype=torch.float32, device="cuda")
+    xd = vitq.QMat.empty(B * N, D, bits)
+    xd.data.copy_(torch.from_numpy(vqo.pack(x, sa)))
+    vitq.vq_attention_block(desc, xd, B, out, ws)
+    torch.cuda.synchronize()
+    qkv = vqo.unpack(dump["qkv"].cpu().numpy(), 64, sa).reshape(3, B, H, N, 64)
+    for which, step in ((0, steps["s_q"]), (1, steps["s_k"])):
+        for h in range(H):
+            sl = slice(which * D + h * 64, which * D + (h + 1) * 64)
+            ref = vqo.layernorm_quantize(y[:, sl], ln["gamma"][sl], ln["beta"][sl], ln["eps"], step, bits)["q"]
+            assert np.array_equal(qkv[which][:, h].reshape(B * N, 64), ref), (which, h)
