@@ -937,7 +937,7 @@ void gemm_kernel(GemmParams p) {
     // been unpacked, so their latency hides behind the MFMAs that follow.  The wait for the next
     // k-stage, the workgroup barrier and the issue of the stage after it sit in the middle of the
     // last sub-step (not between k-steps), where the matrix pipe still holds queued work.
-    constexpr int WRAW = (32 * WB) / 32, XRAW = (32 * AB) / 32;   // dwords of raw data per lane, block and sub-step
+    constexpr int WRAW = WB, XRAW = AB;                           // dwords of raw data per lane, block and sub-step
     u32 wr[NC][WRAW], xr[NTK][XRAW];
     v4i wf[2][NC], xf[2][NTK];
     auto load_raw = [&](int buf, auto SS) {
@@ -961,16 +961,8 @@ void gemm_kernel(GemmParams p) {
         }
 #pragma unroll
         for (int ti = 0; ti < NTK; ++ti) {
-            const uint8_t *src = stage + x_rd[ss][0] + ti * 32 * XROW;
-            if constexpr (AB == 4) {
-                uint4 v = *reinterpret_cast<const uint4 *>(src);
-                xr[ti][0] = v.x; xr[ti][1] = v.y; xr[ti][2] = v.z; xr[ti][3] = v.w;
-            } else {
-                uint4 v0 = *reinterpret_cast<const uint4 *>(src);
-                uint4 v1 = *reinterpret_cast<const uint4 *>(stage + x_rd[ss][XRD - 1] + ti * 32 * XROW);
-                xr[ti][0] = v0.x; xr[ti][1] = v0.y; xr[ti][2] = v0.z; xr[ti][3] = v0.w;
-                xr[ti][4] = v1.x; xr[ti][5] = v1.y; xr[ti][6] = v1.z; xr[ti][7] = v1.w;
-            }
+            const uint4 v = *reinterpret_cast<const uint4 *>(stage + x_rd[ss][0] + ti * 32 * XROW);
+            xr[ti][0] = v.x; xr[ti][1] = v.y; xr[ti][2] = v.z; xr[ti][3] = v.w;
         }
     };
     // raw -> fragment set `fb` for MFMA step s of the current sub-step
@@ -985,13 +977,8 @@ void gemm_kernel(GemmParams p) {
         }
 #pragma unroll
         for (int ti = 0; ti < NTK; ++ti) {
-            if constexpr (AB == 4) {
-                if constexpr (WB == 2) xf[fb][ti] = unpack4_x16_order2(xr[ti][2 * s], xr[ti][2 * s + 1]);
-                else xf[fb][ti] = unpack4_x16(xr[ti][2 * s], xr[ti][2 * s + 1]);
-            } else {
-                xf[fb][ti][0] = (int)xr[ti][4 * s]; xf[fb][ti][1] = (int)xr[ti][4 * s + 1];
-                xf[fb][ti][2] = (int)xr[ti][4 * s + 2]; xf[fb][ti][3] = (int)xr[ti][4 * s + 3];
-            }
+            if constexpr (WB == 2) xf[fb][ti] = unpack4_x16_order2(xr[ti][2 * s], xr[ti][2 * s + 1]);
+            else xf[fb][ti] = unpack4_x16(xr[ti][2 * s], xr[ti][2 * s + 1]);
         }
     };
     auto mma = [&](auto FB) {
@@ -1009,7 +996,7 @@ void gemm_kernel(GemmParams p) {
     // Interleave pattern of one MFMA step: NC*NTK matrix instructions with the unpack arithmetic of
     // the next step spread evenly between them (then, where given, the LDS reads of the next sub-step).
     constexpr int kMma = NC * NTK;
-    constexpr int kUnpackOps = (WB == 8 ? 0 : (WB == 4 ? 6 : 7) * NC) + (AB == 8 ? 0 : (WB == 2 ? 10 : 6) * NTK);
+    constexpr int kUnpackOps = (WB == 8 ? 0 : (WB == 4 ? 6 : 7) * NC) + (WB == 2 ? 10 : 6) * NTK;
     constexpr int kValuPerMma = (kUnpackOps + kMma - 1) / kMma;
     constexpr int kRawReads = NC * WRD + NTK * XRD;
     auto pattern = [&](bool reads_after) {
@@ -1044,7 +1031,7 @@ void gemm_kernel(GemmParams p) {
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-    if constexpr (!(WB == 8 && AB == 8)) {
+    if constexpr (AB == 4) {
     sync_stage(0);
     load_raw(0, I0{});
     unpack(I0{}, I0{});
@@ -1547,8 +1534,10 @@ hipError_t launch_epi(const GemmParams &p, int epi, hipStream_t stream) {
             constexpr int S_HN = (3 * stage <= 80 * 1024) ? 3 : 2;
             return launch<WB, AB, 128, 256, 2, 2, BK, S_HN, 2, kEpiHeadNorm>(p, stream);
         }
-        case kEpiAbsorbed: return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiAbsorbed>(p, stream);
-        case kEpiAbsorbedBig: return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiAbsorbedBig>(p, stream);
+        case kEpiAbsorbed: case kEpiAbsorbedBig:
+            if constexpr (WB == 8 && AB == 4) return hipErrorInvalidValue;       // (expanded weights: the other epilogues' calls only)
+            else if (epi == kEpiAbsorbed) return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiAbsorbed>(p, stream);
+            else return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiAbsorbedBig>(p, stream);
         default: return launch<WB, AB, TC, TT, WAVES_C, WAVES_T, BK, S, OCC, kEpiGeneric>(p, stream);
     }
 }
@@ -1670,7 +1659,7 @@ hipError_t gemm_launch(GemmParams p, int wb, int ab, hipStream_t stream) {
             return hipErrorInvalidValue;
         epi = kEpiHeadNorm;
     }
-    // per-lane operand offsets inside a tile are kept in 32 bits (127 rows * stride + 112)
+    // per-lane operand offsets inside a tile are kept in 32 bits (255 rows * stride + 112)
     if (p.x_stride >= (1 << 24) || p.w_stride >= (1 << 24) || p.M < 1 || p.Nout < 1) return hipErrorInvalidValue;
     if (p.head_major) {
         p.inv_ntok = 1.0f / (float)p.Ntok;

@@ -81,17 +81,15 @@ __device__ __forceinline__ float2 ln_walk_row(const float *xr, const float *rr, 
 
 // Levels of columns c0 .. c0 + 3 of a row by the comparator, one byte each, biased by -qmin.  level = qmin +
 // #{lv : above(lv)}; above() is monotone in lv, so c is the level iff above(c) (or c == qmin) and not above(c + 1) (or
-// c == qmax).  st: mean, guess of 1/(sigma*step), -, V.  from_sum: the row is what sum_out holds already.
-__device__ __forceinline__ u32 ln_compare(const LnParams &p, int64_t row, int c0, const float4 &st, float rstep, bool from_sum) {
+// c == qmax).  st: mean, guess of 1/(sigma*step), -, V.  For rows without a residual.
+__device__ __forceinline__ u32 ln_compare(const LnParams &p, int64_t row, int c0, const float4 &st, float rstep) {
     const int cols = (int)p.cols;
     const float nf = (float)cols, V = st.w, qminf = (float)p.qmin, qmaxf = (float)p.qmax;
     float L[4], bt[4], lv[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int c = min(c0 + i, cols - 1);
-        const int64_t at = row * p.ld + c;
-        const float x = from_sum ? p.sum_out[at] : (p.res ? p.x[at] + p.res[at] : p.x[at]);
-        const float a = x - st.x;
+        const float a = p.x[row * p.ld + c] - st.x;
         const float g = a * p.gamma[c];
         bt[i] = p.beta[c];
         const float gs = g * fabsf(g);
@@ -902,7 +900,7 @@ __global__ __launch_bounds__(kResWaves * 64, 4) void layernorm_resident_kernel(L
                 const int i = __builtin_ctz(redo);
                 redo &= redo - 1;
                 const int q = (kResSets * i + set) * G + g;
-                store_levels(q, ln_compare(p, row0 + row, 4 * q, st, rstep, false));
+                store_levels(q, ln_compare(p, row0 + row, 4 * q, st, rstep));
             }
         }
     }
