@@ -294,7 +294,7 @@ def test_rows_per_workgroup_of_the_one_round_form(rows, cols):
     rng = np.random.default_rng(rows + cols)
     x, gamma, beta = _case(rng, rows, cols)
     _check(x, gamma, beta, 1e-6, np.float32(0.4), 4)
-    _check(x[:3000], gamma, beta, 0.0, np.float32(0.02), 8, ld=None)
+    _check(x, gamma, beta, 0.0, np.float32(0.02), 8)
     big = torch.zeros((rows, cols + 12), device="cuda")
     big[:, :cols] = dev(x)
     out = vitq.QMat.empty(rows, cols, 4, row_stride=(cols // 2 + 15) // 16 * 16 + 32)
@@ -305,3 +305,35 @@ def test_rows_per_workgroup_of_the_one_round_form(rows, cols):
     got = out.data.cpu().numpy()
     want = vqo.pack(vqo.layernorm_quantize(x, gamma, beta, 1e-6, np.float32(0.4), 4)["q"], 4)
     assert np.array_equal(got[:, :row_bytes], want[:, :row_bytes]) and (got[:, row_bytes:] == 0x5A).all()
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("rows,cols", [
+    (4200, 388), (8192, 768), (5000, 772), (8192, 1152),          # up to 32 rows per workgroup, each number of pieces per lane
+    (8200, 260), (16384, 384), (12608, 768), (16384, 500), (9000, 1000), (16384, 1152),       # up to 64
+])
+def test_rows_that_stay_in_registers_many_per_workgroup(rows, cols, bits):
+    """The forms whose walking wave holds more than 16 rows: workgroups from the first to the last by the oracle, with rows of every
+    kind that leaves the fast paths in lanes past 16 and 32, columns on a boundary, bytes past the row untouched."""
+    rng = np.random.default_rng(rows + 1000 * cols + bits)
+    x, gamma, beta = _case(rng, rows, cols)
+    hi, sa = vqo.qrange(bits)[1], storage_of(bits)
+    step = np.float32(2.5 / hi)
+    gamma[::7], beta[::7] = 0.0, step * np.float32(0.5)
+    per = -(-rows // 256)                                          # rows of a workgroup
+    for first in (0, 100 * per):
+        x[first + per - 1] *= 1e-36
+        x[first + per - 2, cols - 1] = 1e4
+        x[first + per - 3] = 0.75
+        x[first + per // 2], x[first + per // 2 + 1, 33], x[first + per // 2 + 2, 1:] = x[first + per // 2] * 1e37, np.nan, 0.0
+    row_bytes = (cols * sa // 8 + 15) // 16 * 16
+    out = vitq.QMat.empty(rows, cols, bits, row_stride=row_bytes + 16)
+    out.data.fill_(0x5A)
+    xd, gd, bd = dev(x), dev(gamma), dev(beta)
+    vitq.vq_layernorm_quantize(xd, None, None, gd, bd, 1e-6, step, out)
+    torch.cuda.synchronize()
+    got = out.data.cpu().numpy()
+    last = (rows - 1) // per * per
+    at = np.unique(np.r_[0:2 * per, 100 * per:101 * per, last - per:rows, rng.integers(0, rows, 150)])
+    want = vqo.pack(vqo.layernorm_quantize(x[at], gamma, beta, 1e-6, step, bits)["q"], sa)
+    assert np.array_equal(got[at, :row_bytes], want[:, :row_bytes]) and (got[:, row_bytes:] == 0x5A).all()

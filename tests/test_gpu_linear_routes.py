@@ -128,7 +128,9 @@ def test_tiled_kernels_on_sampled_rows(bits_x, bits_w, M, K, Nout):
     (4133, 640, 2064),                        # the same of a short contraction: 64 values per stage
     (6304, 800, 4096),                        # 400 tiles of 256x256 for 1,600 small ones (GELU: those)
     (8193, 2400, 2048),                       # 264 for 1,040: two rounds do not pay
-    (16384, 128, 2048), (16385, 2400, 256),   # two even rounds, one stage; a tile of one row and one of 256 channels
+    (16384, 128, 2048),                       # two even rounds, one stage
+    (16385, 2400, 256),                       # 258 small tiles, two units: those, with 128 values per stage
+    (8193, 2400, 1024),                       # 132 tiles of 256x256 for 520, the last four of one row
 ])
 def test_eight_bit_tiles(M, K, Nout):
     """Each 8-bit tile on both sides of the rule that picks it."""

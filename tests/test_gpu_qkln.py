@@ -236,11 +236,10 @@ def test_fused_epilogue_tokens_whose_mean_needs_the_division(bits):
     ln = _ln(D)
     ln["beta"][::9] = 0.0
     steps = dict(s_x=0.5, s_q=np.float32(2.5 / hi), s_k=np.float32(3.0 / hi), s_v=np.float32(3.0 / hi), s_o=0.1, scale=0.125)
-    wd = device_weights(w, bits)
+    wd, gamma, beta = device_weights(w, bits), dev(ln["gamma"]), dev(ln["beta"])     # (the descriptor holds raw pointers)
     x = rng.integers(lo, hi + 1, (B * N, D)).astype(np.int8)
     dump = {"qkv": torch.zeros((3 * B * H * N, 64 * sa // 8), dtype=torch.uint8, device="cuda")}
-    desc = vitq.make_block_desc(dims, bits, bits, sa, wd, steps, dump,
-                                qkln=dict(gamma=dev(ln["gamma"]), beta=dev(ln["beta"]), eps=ln["eps"]))
+    desc = vitq.make_block_desc(dims, bits, bits, sa, wd, steps, dump, qkln=dict(gamma=gamma, beta=beta, eps=ln["eps"]))
     ws = torch.empty(vitq.vq_attention_block_workspace(desc, B), dtype=torch.uint8, device="cuda")
     y = torch.empty((B * N, D), dtype=torch.float32, device="cuda")
     xd = vitq.QMat.empty(B * N, D, bits)
