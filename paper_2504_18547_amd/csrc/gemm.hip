@@ -1603,7 +1603,8 @@ bool small_tile(const GemmParams &p, int epi) {
 // most of all).  What decides is the busiest CU's work in units of 128x128, times what the form takes per unit.  us of
 // kSmall / kDeep / kLarge, outputs fp32 (f), requantized (q), GELU (g), calls repeated until the clock is steady, in
 // parentheses the units of the small tiles and of the large one:
-//   (1, 4)  5,193 x 1024 -> 1024 q 13.8 / 12.5 / 17 (up to two units: kDeep is ahead or level everywhere)
+//   (1, 4)  5,193 x 1024 -> 1024 q 13.8 / 12.5 / 17 (up to two units kDeep is ahead by 2 to 20 %, by 1 to 7 % behind where K up
+//           to 192 does not fill its second stage, 2,247 x 192 -> 2368 q 8.4 / 8.8)
 //   (3, 4)  12,608 x 3072 -> 768 f 48.5 / 46.2 / 38.2, q 49.4 / 48.4 / 38.6, g 52.1 / 52.7 / 45.3; K 768 f 18.1 / 19.9 / 16.9,
 //           q 17.9 / 18.9 / 16.6, g 22.3 / 23.1 / 24.4; 25,216 x 384 -> 384 f 12.8 / 14.1 / 13.4; x 1536 g 31.6 / 34.2 / 33.9
 //   (4, 4)  12,608 x 384 -> 1152 f 18.7 / 17.2 / 16.9, q 17.5 / 17.2 / 15.4, g 23.0 / 23.7 / 23.5
@@ -1615,10 +1616,16 @@ bool small_tile(const GemmParams &p, int epi) {
 //           q 27.3 / 29.9 / 28.3
 //   (25, 28)  25,216 x 4096 -> 1024 f 150 / 127 / 113, q 149 / 130 / 111, g 152 / 136 / 123
 //   (74, 76)  25,216 x 1024 -> 3072 f 147 / 143 / 121, q 118 / 120 / 107, g 136 / 140 / 142
+// Of fp32 results on an even deal of several rounds the stores take most of the time up to K 320 (kSmall / kLarge: 34,763 x 256
+// -> 2752, 24 units each, 85.5 / 93.8; 12,856 x 128 -> 3520 38.5 / 39.6; 45,892 x 176 -> 960 41.2 / 44.1; from there on kLarge
+// is ahead, 16,384 x 336 -> 4096 90.0 / 76.8), and in two rounds up to 512 where rows are whole cache lines, which kSmall does
+// not read twice from L2 (8,992 x 384 -> 3264 35.7 / 40.9, x 512 40.0 / 42.5; x 400 44.1 / 40.7).  GELU of K 2048 and more:
+// 30,024 x 2249 -> 1952 255 / 203, 47,258 x 2165 -> 1088 176 / 176, 17,989 x 2166 -> 3488 221 / 182.
 // A dense kernel that holds the chip for long also holds its clock down for the kernels around it: in the ViT-B block of
 // 128 images, calls in a row, kLarge for its QKV linear (14, 16) and kDeep for its fc2 (5, 8) cost the block 376 -> 400 us
 // although each saves 1 to 12 us by itself, the attention between them going from 72 to 77.  So kLarge has to be ahead by
-// a twelfth past eight units (the figures below contain it), and kDeep is for calls too small to matter (one at a time, 25,216 x 3072 -> 768
+// a twelfth past eight units (the figures below contain it; a caller of one such linear alone pays for it: the (14, 16) and
+// (5, 8) rows of K 768 and 3072 above, by up to 12 and 14 %), and kDeep is for calls too small to matter (one at a time, 25,216 x 3072 -> 768
 // 161.5 us with its quantizer on kSmall, 163.7 on kDeep; 25,216 x 1024 -> 3072 143 on kSmall, 132 on kLarge).  The 128x256
 // tile on four waves that long contractions took before is behind by 2 to 25 % wherever it ran.
 enum class Tile8 { kSmall, kDeep, kLarge };
@@ -1628,11 +1635,12 @@ Tile8 tile8(const GemmParams &p, int epi) {
     const int64_t large = (int64_t)((p.Nout + 255) / 256) * (((int64_t)p.M + 255) / 256);
     const int64_t cs = (small + kCUs - 1) / kCUs, cl = 4 * ((large + kCUs - 1) / kCUs);       // units of the busiest CU
     const bool gelu = epi == kEpiQuantGelu, one_round = large <= kCUs;
-    if (cs <= 2) return Tile8::kDeep;
+    const bool lines = p.x_stride % 128 == 0 && p.w_stride % 128 == 0;           // rows of whole cache lines
+    if (cs <= 2) return p.K > 192 ? Tile8::kDeep : Tile8::kSmall;
     int unit;                                       // of kLarge, in hundredths of kSmall's
-    if (p.K >= (gelu ? 2304 : 1536)) unit = gelu && !one_round ? 76 : 65;
+    if (p.K >= (gelu ? 2048 : 1536)) unit = gelu && !one_round ? 76 : 65;
     else if (p.K >= 768) unit = one_round ? (gelu ? 82 : 65) : (gelu ? 108 : (cs <= 8 ? 84 : 91));
-    else unit = gelu ? 108 : (one_round ? 82 : (epi == kEpiF32 ? 95 : 104));
+    else unit = gelu ? 108 : (one_round ? 82 : (epi == kEpiF32 && p.K >= (lines && cl <= 8 ? 513 : 320) ? 95 : 104));
     return unit * cl < 100 * cs ? Tile8::kLarge : Tile8::kSmall;
 }
 
