@@ -1621,13 +1621,17 @@ bool small_tile(const GemmParams &p, int epi) {
 // is ahead, 16,384 x 336 -> 4096 90.0 / 76.8), and in two rounds up to 512 where rows are whole cache lines, which kSmall does
 // not read twice from L2 (8,992 x 384 -> 3264 35.7 / 40.9, x 512 40.0 / 42.5; x 400 44.1 / 40.7).  GELU of K 2048 and more:
 // 30,024 x 2249 -> 1952 255 / 203, 47,258 x 2165 -> 1088 176 / 176, 17,989 x 2166 -> 3488 221 / 182.
+// Four units are two even rounds of kDeep and one and a third of kSmall, which a long contraction pays for in full (7,446 x 4096 ->
+// 2096 f 99.3 / 85.9, q 95.0 / 73.4; 33,721 x 2048 -> 368 f 55.4 / 50.1); five are three rounds against two, ahead only where
+// rows are no whole cache lines (9,239 x 3043 -> 2144 f 120 / 103, q 105 / 91.5; 33,935 x 2432 -> 512 f 73.9 / 79.1).
 // A dense kernel that holds the chip for long also holds its clock down for the kernels around it: in the ViT-B block of
 // 128 images, calls in a row, kLarge for its QKV linear (14, 16) and kDeep for its fc2 (5, 8) cost the block 376 -> 400 us
 // although each saves 1 to 12 us by itself, the attention between them going from 72 to 77.  So kLarge has to be ahead by
 // a twelfth past eight units (the figures below contain it; a caller of one such linear alone pays for it: the (14, 16) and
 // (5, 8) rows of K 768 and 3072 above, by up to 12 and 14 %), and kDeep is for calls too small to matter (one at a time, 25,216 x 3072 -> 768
 // 161.5 us with its quantizer on kSmall, 163.7 on kDeep; 25,216 x 1024 -> 3072 143 on kSmall, 132 on kLarge).  The 128x256
-// tile on four waves that long contractions took before is behind by 2 to 25 % wherever it ran.
+// tile on four waves that long contractions took before is behind by 2 to 25 % but in calls of four units, where kDeep takes up to
+// 5 % longer (37,142 x 2176 -> 288 q 44.5 us, 46.3).
 enum class Tile8 { kSmall, kDeep, kLarge };
 Tile8 tile8(const GemmParams &p, int epi) {
     constexpr int64_t kCUs = 256;
@@ -1641,7 +1645,8 @@ Tile8 tile8(const GemmParams &p, int epi) {
     if (p.K >= (gelu ? 2048 : 1536)) unit = gelu && !one_round ? 76 : 65;
     else if (p.K >= 768) unit = one_round ? (gelu ? 82 : 65) : (gelu ? 108 : (cs <= 8 ? 84 : 91));
     else unit = gelu ? 108 : (one_round ? 82 : (epi == kEpiF32 && p.K >= (lines && cl <= 8 ? 513 : 320) ? 95 : 104));
-    return unit * cl < 100 * cs ? Tile8::kLarge : Tile8::kSmall;
+    if (unit * cl < 100 * cs) return Tile8::kLarge;
+    return p.K >= 2048 && (cs == 4 || (cs == 5 && !lines)) ? Tile8::kDeep : Tile8::kSmall;
 }
 
 }  // namespace

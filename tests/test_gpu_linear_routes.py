@@ -130,6 +130,7 @@ def test_tiled_kernels_on_sampled_rows(bits_x, bits_w, M, K, Nout):
     (8193, 2400, 2048),                       # 264 for 1,040: two rounds do not pay
     (16384, 128, 2048),                       # two even rounds, one stage
     (16385, 2400, 256),                       # 258 small tiles, two units: those, with 128 values per stage
+    (5630, 2219, 2848),                       # 1012 small tiles, four units: 128 values per stage
     (1500, 192, 1040), (1500, 193, 1040),     # one unit: 64 values per stage, 128
     (16300, 333, 2048), (16300, 384, 2048),   # two even rounds in fp32: 256x256, and 128x128 where rows are whole cache lines
     (8193, 2400, 1024),                       # 132 tiles of 256x256 for 520, the last four of one row
