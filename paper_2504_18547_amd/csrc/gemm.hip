@@ -1625,13 +1625,15 @@ bool small_tile(const GemmParams &p, int epi) {
 // 2096 f 99.3 / 85.9, q 95.0 / 73.4; 33,721 x 2048 -> 368 f 55.4 / 50.1); five are three rounds against two, ahead only where
 // rows are no whole cache lines (9,239 x 3043 -> 2144 f 120 / 103, q 105 / 91.5; 33,935 x 2432 -> 512 f 73.9 / 79.1).
 // A dense kernel that holds the chip for long also holds its clock down for the kernels around it: in the ViT-B block of
-// 128 images, calls in a row, kLarge for its QKV linear (14, 16) and kDeep for its fc2 (5, 8) cost the block 376 -> 400 us
-// although each saves 1 to 12 us by itself, the attention between them going from 72 to 77.  So kLarge has to be ahead by
-// a twelfth past eight units (the figures below contain it; a caller of one such linear alone pays for it: the (14, 16) and
-// (5, 8) rows of K 768 and 3072 above, by up to 12 and 14 %), and kDeep is for calls too small to matter (one at a time, 25,216 x 3072 -> 768
-// 161.5 us with its quantizer on kSmall, 163.7 on kDeep; 25,216 x 1024 -> 3072 143 on kSmall, 132 on kLarge).  The 128x256
-// tile on four waves that long contractions took before is behind by 2 to 25 % but in calls of four units, where kDeep takes up to
-// 5 % longer (37,142 x 2176 -> 288 q 44.5 us, 46.3).
+// 128 images, calls in a row, kLarge for its QKV linear (14, 16) costs the block 385 -> 406 us and kDeep for its fc2 (5, 8) 400,
+// although each saves 1 to 12 us by itself (the attention between them goes from 72 to 77).  The same in blocks of other
+// sizes with those units: 43 images of 577 tokens 582 -> 612 and 610, 500 of 50 393 -> 411 and 407, 128 of 198 387 -> 407 and
+// 402.  It is the power that operands of a real spread draw: with nearly constant levels kDeep gains the same blocks 1 to 2 %.
+// So kLarge has to be ahead by a twelfth past eight units (the figures below contain it), and kDeep is for calls too
+// small to matter and where kSmall falls behind for good.  A caller of one such linear alone pays for it, the (14, 16) and
+// (5, 8) rows of K 768 and 3072 above, by up to 12 and 14 % with the clock up.  The 128x256 tile on four waves that long
+// contractions took before is behind by 2 to 25 % but in calls of four units, where kDeep takes up to 5 % longer (37,142 x
+// 2176 -> 288 q 44.5 us, 46.3).
 enum class Tile8 { kSmall, kDeep, kLarge };
 Tile8 tile8(const GemmParams &p, int epi) {
     constexpr int64_t kCUs = 256;
